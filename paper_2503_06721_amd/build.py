@@ -2,8 +2,8 @@
 
     python -m paper_2503_06721_amd.build          # or build() from Python
 
-Every HIP source is compiled to an object under _build/ (in parallel), then
-linked into paper_2503_06721_amd/libwdirac.so next to this file.
+Every HIP source is compiled to an object under _build/ (in parallel; the
+hop sources, whose kernels are many, in parts), then linked into paper_2503_06721_amd/libwdirac.so next to this file.
 """
 import concurrent.futures
 import os
@@ -14,7 +14,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, 'csrc')
 BUILD = os.path.join(HERE, '_build')
 LIB = os.path.join(HERE, 'libwdirac.so')
-SOURCES = ['api.hip', 'hop.hip', 'hop_mr.hip', 'rep.hip', 'blas.hip', 'force.hip', 'stream.hip', 'clover.hip', 'hmc.hip']
+SOURCES = ['api.hip', 'rep.hip', 'blas.hip', 'force.hip', 'stream.hip', 'clover.hip', 'hmc.hip']
+# (source, WD_PART): each part holds the kernels of some precisions, projectors
+# and representation dimensions (the longest first)
+PARTS = [('hop.hip', k) for k in range(8)] + [('hop_mr.hip', k) for k in range(4)]
 HIPCC = os.environ.get('HIPCC', '/opt/rocm/bin/hipcc')
 ARCH = 'gfx950'
 FLAGS = [
@@ -25,9 +28,11 @@ FLAGS = [
 ]
 
 
-def _compile(src):
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + '.o')
-    cmd = [HIPCC, *FLAGS, '-I', CSRC, '-c', os.path.join(CSRC, src), '-o', obj]
+def _compile(job):
+    src, part = job
+    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ('' if part is None else f'_{part}') + '.o')
+    define = [] if part is None else [f'-DWD_PART={part}']
+    cmd = [HIPCC, *FLAGS, *define, '-I', CSRC, '-c', os.path.join(CSRC, src), '-o', obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f'hipcc failed on {src}:\n{" ".join(cmd)}\n{res.stdout}\n{res.stderr}')
@@ -37,9 +42,10 @@ def _compile(src):
 def build(verbose=False, jobs=None):
     """Compile every HIP source for gfx950 and link libwdirac.so.  Always rebuilds."""
     os.makedirs(BUILD, exist_ok=True)
-    jobs = jobs or min(len(SOURCES), max(1, (os.cpu_count() or 2)))
+    work = PARTS + [(src, None) for src in SOURCES]
+    jobs = jobs or min(len(work), max(1, (os.cpu_count() or 2)))
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, work))
     tmp = LIB + '.tmp'
     cmd = [HIPCC, '-shared', '-fPIC', f'--offload-arch={ARCH}', *objs, '-o', tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -207,11 +207,22 @@ int effective_nr(const wdirac_ctx *c, int pref, int nrhs, int prec, int variant)
   return 1;
 }
 
+// What a hop of a CG iteration does beside hopping (wd_kernels.h, HopArgs):
+// the alpha step from the partial sums lp, or the update of the residual r.
+struct CgHop {
+  wd::CgScalars *sc;
+  int nsys;             // leading blocks of the alpha step (0: none)
+  const double *lp;
+  int lprow;
+  wd::Counts lcnt;
+  void *r;              // nullable
+};
+
 // One hopping-term launch over every lattice of the context.  counts/prow
 // (nullable) receive the layout of the per-tile partial sums.
 int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_parity, int dagger, int nrhs,
         double alpha, const void *xadd, double beta, int prec, double *partial, hipStream_t st,
-        wd::Counts *counts = nullptr, int *prow = nullptr) {
+        wd::Counts *counts = nullptr, int *prow = nullptr, const CgHop *cg = nullptr) {
   int variant = c->hop_variant[prec], pref = c->hop_nr[prec], remap = c->xcd_remap, tblock = c->tblock;
   const wdirac_tuned &tn = c->tuned[prec][nrhs];
   if (tn.valid) {
@@ -242,6 +253,12 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
   a.prow = a.ntiles = a.ngroups = 0;
   a.tblock = c->nlat == 1 ? tblock : 0;
   a.tiles_per_tx = 0;
+  a.sc = cg ? cg->sc : nullptr;
+  a.lead = cg ? cg->nsys : 0;
+  a.lp = cg ? cg->lp : nullptr;
+  a.lprow = cg ? cg->lprow : 0;
+  a.lcnt = cg ? cg->lcnt : wd::Counts{};
+  a.r = cg ? cg->r : nullptr;
   wd::Counts cnt{};
   int pr = 0;
   WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, variant,
@@ -269,20 +286,18 @@ int clover_apply(const wdirac_ctx *c, void *out, const void *in, const void *clo
 // Without a clover field: D-hat = (4+m)^2 - D_eo D_oe (Sec. 5.3.3, one factor
 // of 4+m absorbed).  With one: D-hat = D_ee - D_eo D_oo^{-1} D_oe, whose
 // diagonal blocks are Hermitian, so the adjoint only swaps to the dagger hops.
+// cg1, cg2 (nullable): what the first and the second hop do for a CG iteration.
 int dhat(const wdirac_ctx *c, void *out, const void *in, const void *UR, double m0, int dagger, int nrhs, int prec,
          void *tmp, double *partial, hipStream_t st, wd::Counts *counts = nullptr, int *prow = nullptr,
-         const void *clov = nullptr) {
+         const void *clov = nullptr, const CgHop *cg1 = nullptr, const CgHop *cg2 = nullptr) {
+  WD_TRY(hop(c, tmp, in, UR, 1, dagger, nrhs, 0.0, nullptr, 1.0, prec, nullptr, st, nullptr, nullptr, cg1));
   if (clov) {
-    WD_TRY(hop(c, tmp, in, UR, 1, dagger, nrhs, 0.0, nullptr, 1.0, prec, nullptr, st));
     WD_TRY(clover_apply(c, tmp, tmp, clov, 1, nrhs, prec, st));
     WD_TRY(clover_apply(c, out, in, clov, 0, nrhs, prec, st));
-    WD_TRY(hop(c, out, tmp, UR, 0, dagger, nrhs, 1.0, out, -1.0, prec, partial, st, counts, prow));
-    return WDIRAC_OK;
+    return hop(c, out, tmp, UR, 0, dagger, nrhs, 1.0, out, -1.0, prec, partial, st, counts, prow, cg2);
   }
-  const double m4 = (4.0 + m0) * (4.0 + m0);
-  WD_TRY(hop(c, tmp, in, UR, 1, dagger, nrhs, 0.0, nullptr, 1.0, prec, nullptr, st));
-  WD_TRY(hop(c, out, tmp, UR, 0, dagger, nrhs, m4, in, -1.0, prec, partial, st, counts, prow));
-  return WDIRAC_OK;
+  return hop(c, out, tmp, UR, 0, dagger, nrhs, (4.0 + m0) * (4.0 + m0), in, -1.0, prec, partial, st, counts, prow,
+             cg2);
 }
 
 // Canonical <-> packed half spinors, lattice by lattice.  Canonical batch
@@ -937,7 +952,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
 
   // b2, stop2
   WD_HIP(wd::launch_norm2_partial(w.P2, b, f, WDIRAC_F64, st));
-  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 1, 1, st));
+  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 1, st));
   // r = b - A x (FP64)
   auto true_residual = [&]() -> int {
     WD_TRY(dhat(ctx, w.u, x, UR64, m0, 0, nrhs, WDIRAC_F64, w.t, nullptr, st, nullptr, nullptr, clov64));
@@ -947,7 +962,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
     return WDIRAC_OK;
   };
   WD_TRY(true_residual());
-  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, 1, st));
+  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, st));
   void *r = w.r, *p = w.p, *q = w.q, *t = w.t, *u = w.u, *v = w.v, *xi = x;
   const void *UR = UR64, *clov = clov64;
   int prec = WDIRAC_F64;
@@ -984,7 +999,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
       // residual replacement in FP64 (verifies convergence of the recursion)
       if (mixed) WD_HIP(wd::launch_accum_x(x, w.x32, f, st));
       WD_TRY(true_residual());
-      WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, 0, st));
+      WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, st));
       if (mixed) WD_HIP(wd::launch_convert(w.r32, WDIRAC_F32, w.r, WDIRAC_F64, f, st));
       ++updates;
       for (int k = 0; k < ns; ++k)
@@ -1001,12 +1016,13 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
       for (int it = 0; it < n; ++it) {
         wd::Counts cnt{};
         int prow = 0;
+        // u = D-hat p with ||u||^2; then A p = D-hat^+ u: alpha beside the
+        // first of its hops, r -= alpha A p in the second (A p itself is not
+        // stored; q holds D_ee u of the clover form)
         WD_TRY(dhat(ctx, u, p, UR, m0, 0, nrhs, prec, t, w.P1, st, &cnt, &prow, clov));
-        WD_HIP(wd::launch_cg_alpha(w.sc, w.P1, prow, cnt, ns, st));
-        WD_TRY(dhat(ctx, q, u, UR, m0, 1, nrhs, prec, v, nullptr, st, nullptr, nullptr, clov));
-        WD_HIP(wd::launch_cg_update_xr(xi, prec, r, p, q, w.sc, w.P2, f, prec, st));
-        WD_HIP(wd::launch_cg_beta(w.sc, w.P2, nbb, ns, delta, st));
-        WD_HIP(wd::launch_cg_update_p(p, r, w.sc, f, prec, st));
+        const CgHop ca{w.sc, ns, w.P1, prow, cnt, nullptr}, cr{w.sc, 0, nullptr, 0, {}, r};
+        WD_TRY(dhat(ctx, q, u, UR, m0, 1, nrhs, prec, v, w.P2, st, &cnt, &prow, clov, &ca, &cr));
+        WD_HIP(wd::launch_cg_update_xp(xi, p, r, w.sc, w.P2, prow, cnt, delta, f, prec, st));
       }
       return WDIRAC_OK;
     };

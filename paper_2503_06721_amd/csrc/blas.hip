@@ -34,60 +34,6 @@ __device__ __forceinline__ cplx<double> up(cplx<T> v) {
   return mk<double>((double)v.re, (double)v.im);
 }
 
-// Compensated accumulation (Neumaier): (s, c) += v.
-__device__ __forceinline__ void neumaier_add(double &s, double &c, double v) {
-  const double t = s + v;
-  if (fabs(s) >= fabs(v)) c += (s - t) + v;
-  else c += (v - t) + s;
-  s = t;
-}
-
-// Error-free transformation: s + e == a + b exactly (Knuth's TwoSum, no
-// ordering requirement on |a|, |b|).
-__device__ __forceinline__ void two_sum(double a, double b, double &s, double &e) {
-  s = a + b;
-  const double bb = s - a;
-  e = (a - (s - bb)) + (b - bb);
-}
-
-// One block per rhs: compensated sum of partial[0..nblk).  Each thread keeps a
-// Neumaier (sum, compensation) pair over a strided subset; pairs are merged
-// by a butterfly over the wavefront with TwoSum on the sums, then the four
-// wavefronts are merged in a fixed order.  Deterministic: the result depends
-// only on nblk and the values, not on timing.
-__device__ double sum_partials(const double *partial, int nblk) {
-  __shared__ double ws[BT / 64], wc[BT / 64];
-  double s = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += BT) neumaier_add(s, c, partial[k]);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const double so = __shfl_xor(s, off, 64), co = __shfl_xor(c, off, 64);
-    double t, e;
-    two_sum(s, so, t, e);
-    s = t;
-    c = (c + co) + e;
-  }
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    ws[threadIdx.x >> 6] = s;
-    wc[threadIdx.x >> 6] = c;
-  }
-  __syncthreads();
-  double tot = 0.0;
-  if (threadIdx.x == 0) {
-    double ts = ws[0], tc = wc[0];
-    for (int w = 1; w < BT / 64; ++w) {
-      double t, e;
-      two_sum(ts, ws[w], t, e);
-      ts = t;
-      tc = (tc + wc[w]) + e;
-    }
-    tot = ts + tc;
-  }
-  __syncthreads();
-  return tot;
-}
-
 __global__ __launch_bounds__(BT) void k_finalize_sum(double *out, const double *partial, int prow, Counts cnt,
                                                      int nsys) {
   const int r = blockIdx.x;
@@ -208,137 +154,120 @@ hipError_t launch_convert(void *out, int prec_out, const void *in, int prec_in, 
 }
 
 // ------------------------------------------------------------------- CG
-__global__ __launch_bounds__(BT) void k_cg_alpha(CgScalars *S, const double *partial, int prow, Counts cnt) {
-  const int r = blockIdx.x;
-  CgScalars &s = S[r];
-  if (!s.active) return;
-  const double pAp = sum_partials(partial + (size_t)r * prow, cnt.n[r]);
-  if (threadIdx.x == 0) {
-    s.pAp = pAp;
-    if (!(pAp > 0.0) || !isfinite(pAp) || !isfinite(s.rho)) {
-      s.status = -5;   // breakdown
-      s.active = 0;
-      s.alpha = 0.0;
-    } else {
-      s.alpha = s.rho / pAp;
-    }
+// State of a system at the end of an iteration, rr = |r|^2 after it (thread 0
+// of one block).
+__device__ __forceinline__ void cg_end_step(CgScalars &s, double rr, double delta) {
+  s.iters += 1;
+  if (!isfinite(rr)) {
+    s.status = -5;
+    s.active = 0;
+    return;
+  }
+  s.rho = rr;
+  const double rn = sqrt(rr);
+  if (rn > s.rmax) s.rmax = rn;
+  if (rr <= s.stop2) {
+    s.active = 0;          // recursive residual converged: verify in FP64
+    s.need_update = 1;
+  } else if (delta > 0.0 && rn < delta * s.rmax) {
+    // mixed mode: ask for a reliable update and keep iterating until every
+    // other active system asks too, so that no system idles while the
+    // batched hops still stream its field
+    s.need_update = 1;
   }
 }
 
-hipError_t launch_cg_alpha(CgScalars *s, const double *pAp_partial, int prow, const Counts &counts, int nsys,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_alpha, dim3(nsys), dim3(BT), 0, st, s, pAp_partial, prow, counts);
-  return hipGetLastError();
+// The sum and the state update as a kernel of their own, one block per system.
+__global__ __launch_bounds__(1024) void k_cg_end(CgScalars *S, const double *__restrict__ rr_partial, int prow,
+                                                 Counts cnt, double delta) {
+  CgScalars &s = S[blockIdx.x];
+  if (!s.act_it) return;
+  const double rr = sum_partials(rr_partial + (size_t)blockIdx.x * prow, cnt.n[blockIdx.x]);
+  if (threadIdx.x != 0) return;
+  s.rr = rr;
+  cg_end_step(s, rr, delta);
 }
 
-template <typename T, typename TX>
-__global__ __launch_bounds__(BT) void k_cg_update_xr(void *x, void *r, const void *p, const void *q,
-                                                     const CgScalars *S, double *partial, FieldShape f) {
-  __shared__ double sh[BT / 64];
-  const CgScalars &s = S[blockIdx.y];
-  if (!s.active) return;
-  const double a = s.alpha;
-  const int i = blockIdx.x * BT + threadIdx.x, sy = blockIdx.y;
-  double nrm = 0.0;
-  if (i < f.vh[sy]) {
-    const size_t base = (size_t)f.off[sy] + i;
-    for (int c = 0; c < f.ncomp; ++c) {
-      const size_t o = base + (size_t)c * f.stride[sy];
-      const cplx<double> pv = up(ld<T>(p, o)), qv = up(ld<T>(q, o));
-      cplx<double> xv = up(ld<TX>(x, o)), rv = up(ld<T>(r, o));
-      xv.re = fma(a, pv.re, xv.re);
-      xv.im = fma(a, pv.im, xv.im);
-      rv.re = fma(-a, qv.re, rv.re);
-      rv.im = fma(-a, qv.im, rv.im);
-      st<TX>(x, o, xv);
-      const cplx<T> rs = mk<T>((T)rv.re, (T)rv.im);   // the stored (rounded) residual
-      static_cast<cplx<T> *>(r)[o] = rs;
-      nrm += (double)rs.re * rs.re + (double)rs.im * rs.im;
+// End of an iteration: beta = rho'/rho from the partial sums of |r|^2 that the
+// last hop left, x += alpha p, p = r + beta p, and the state of the system
+// (convergence, and in mixed mode the reliable-update trigger).
+//
+// Bound by memory: x, p read and written, r read (5 half fields; with r's own
+// update in the hop an iteration moves 6 beside its hops instead of 9 and a
+// stored A p): 6.1 TB/s on SU(3) FUND 32^4 (FP32 41 us, where the separate
+// x, r and p updates took 72).  Up to kOwnSum partial sums every block adds
+// them up itself (OWN), which costs less than a launch between the hop and
+// this kernel; the first block of a system then stores the state, whose
+// fields no block reads here.  Longer rows are summed by k_cg_end (2592
+// partial sums, SU(3) FUND 24^4: 32.1 us with them, 27.6 + 5.5 us and a launch
+// apart; 8192, 32^4 FP32: 47.1 against 40.9 + 5.5 us).
+// Thread per site and, by blockIdx.z, group of `per` components: all 4 d of
+// them where the sites alone give every CU four blocks, else four, which
+// shortens the chain of loads of a small lattice (SU(2) ADJ 32x16^3: 15.1 us,
+// the separate updates 23.6; SU(2) FUND 4^4: 3.7, they 7.9).
+constexpr int kOwnSum = 4096;
+template <typename T, bool OWN>
+__global__ __launch_bounds__(BT) void k_cg_update_xp(cplx<T> *__restrict__ x, cplx<T> *__restrict__ p,
+                                                     const cplx<T> *__restrict__ r, CgScalars *S,
+                                                     const double *__restrict__ rr_partial, int prow, Counts cnt,
+                                                     double delta, int per, FieldShape f) {
+  const int sy = blockIdx.y;
+  CgScalars &s = S[sy];
+  if (!s.act_it) return;
+  const double a = s.alpha, rho = s.rho_it;
+  double rr;
+  if constexpr (OWN) {
+    rr = sum_partials(rr_partial + (size_t)sy * prow, cnt.n[sy]);
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) cg_end_step(s, rr, delta);
+  } else {
+    rr = s.rr;
+  }
+  const bool ok = isfinite(rr);
+  const int i = blockIdx.x * BT + threadIdx.x;
+  if (i >= f.vh[sy]) return;
+  const double b = rr / rho;
+  const size_t st = f.stride[sy];
+  const size_t base = (size_t)f.off[sy] + i + (size_t)blockIdx.z * per * st;
+  for (int c = 0; c < per; c += 4) {
+    cplx<T> pv[4], xv[4], rv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const size_t o = base + (size_t)(c + k) * st;
+      pv[k] = p[o];
+      xv[k] = x[o];
+      rv[k] = r[o];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const size_t o = base + (size_t)(c + k) * st;
+      x[o] = mk<T>((T)fma(a, (double)pv[k].re, (double)xv[k].re), (T)fma(a, (double)pv[k].im, (double)xv[k].im));
+      // a residual that is not finite ends the system before its p update
+      if (ok)
+        p[o] = mk<T>((T)fma(b, (double)pv[k].re, (double)rv[k].re), (T)fma(b, (double)pv[k].im, (double)rv[k].im));
     }
   }
-  nrm = block_sum(nrm, sh);
-  if (threadIdx.x == 0) partial[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = nrm;
-}
-
-hipError_t launch_cg_update_xr(void *x, int prec_x, void *r, const void *p, const void *q, const CgScalars *s,
-                               double *partial, const FieldShape &f, int prec, hipStream_t st) {
-  dim3 grid(blas_nblocks(f), f.nsys);
-  if (prec == 0 && prec_x == 0)
-    hipLaunchKernelGGL((k_cg_update_xr<double, double>), grid, dim3(BT), 0, st, x, r, p, q, s, partial, f);
-  else if (prec == 1 && prec_x == 1)
-    hipLaunchKernelGGL((k_cg_update_xr<float, float>), grid, dim3(BT), 0, st, x, r, p, q, s, partial, f);
-  else if (prec == 1 && prec_x == 0)
-    hipLaunchKernelGGL((k_cg_update_xr<float, double>), grid, dim3(BT), 0, st, x, r, p, q, s, partial, f);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-// beta = rho'/rho; convergence and (mixed mode) reliable-update triggers.
-// The p update of an iteration is due exactly when this kernel ran for the rhs
-// (do_p), including the iteration that pauses it for a residual replacement:
-// the recurrence resumes afterwards from a consistent (r, p) pair.
-__global__ __launch_bounds__(BT) void k_cg_beta(CgScalars *S, const double *partial, int nblk, double delta) {
-  const int r = blockIdx.x;
-  CgScalars &s = S[r];
-  const int act = s.active;
-  __syncthreads();
-  if (threadIdx.x == 0) s.do_p = 0;
-  if (!act) return;
-  const double rr = sum_partials(partial + (size_t)r * nblk, nblk);
-  if (threadIdx.x == 0) {
-    s.iters += 1;
-    if (!isfinite(rr)) {
-      s.status = -5;
-      s.active = 0;
-      return;
-    }
-    s.beta = rr / s.rho;
-    s.rho = rr;
-    s.do_p = 1;
-    const double rn = sqrt(rr);
-    if (rn > s.rmax) s.rmax = rn;
-    if (rr <= s.stop2) {
-      s.active = 0;          // recursive residual converged: verify in FP64
-      s.need_update = 1;
-    } else if (delta > 0.0 && rn < delta * s.rmax) {
-      // mixed mode: ask for a reliable update and keep iterating until every
-      // other active system asks too, so that no system idles while the
-      // batched hops still stream its field
-      s.need_update = 1;
-    }
-  }
-}
-
-hipError_t launch_cg_beta(CgScalars *s, const double *rr_partial, int nblk, int nrhs, double delta,
-                          hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_beta, dim3(nrhs), dim3(BT), 0, st, s, rr_partial, nblk, delta);
-  return hipGetLastError();
 }
 
 template <typename T>
-__global__ __launch_bounds__(BT) void k_cg_update_p(void *p, const void *r, const CgScalars *S, FieldShape f) {
-  const CgScalars &s = S[blockIdx.y];
-  if (!s.do_p) return;
-  const double b = s.beta;
-  const int i = blockIdx.x * BT + threadIdx.x, sy = blockIdx.y;
-  if (i >= f.vh[sy]) return;
-  const size_t base = (size_t)f.off[sy] + i;
-  for (int c = 0; c < f.ncomp; ++c) {
-    const size_t o = base + (size_t)c * f.stride[sy];
-    const cplx<double> rv = up(ld<T>(r, o));
-    cplx<double> pv = up(ld<T>(p, o));
-    pv.re = fma(b, pv.re, rv.re);
-    pv.im = fma(b, pv.im, rv.im);
-    st<T>(p, o, pv);
+static void update_xp(void *x, void *p, const void *r, CgScalars *s, const double *rr_partial, int prow,
+                      const Counts &counts, double delta, const FieldShape &f, hipStream_t st) {
+  const int nb = blas_nblocks(f);
+  const int per = nb * f.nsys >= 1024 ? f.ncomp : 4;
+  const dim3 grid(nb, f.nsys, f.ncomp / per);
+  if (prow <= kOwnSum) {
+    hipLaunchKernelGGL((k_cg_update_xp<T, true>), grid, dim3(BT), 0, st, (cplx<T> *)x, (cplx<T> *)p,
+                       (const cplx<T> *)r, s, rr_partial, prow, counts, delta, per, f);
+  } else {
+    hipLaunchKernelGGL(k_cg_end, dim3(f.nsys), dim3(1024), 0, st, s, rr_partial, prow, counts, delta);
+    hipLaunchKernelGGL((k_cg_update_xp<T, false>), grid, dim3(BT), 0, st, (cplx<T> *)x, (cplx<T> *)p,
+                       (const cplx<T> *)r, s, rr_partial, prow, counts, delta, per, f);
   }
 }
 
-hipError_t launch_cg_update_p(void *p, const void *r, const CgScalars *s, const FieldShape &f, int prec,
-                              hipStream_t st) {
-  dim3 grid(blas_nblocks(f), f.nsys);
-  if (prec == 0) hipLaunchKernelGGL(k_cg_update_p<double>, grid, dim3(BT), 0, st, p, r, s, f);
-  else hipLaunchKernelGGL(k_cg_update_p<float>, grid, dim3(BT), 0, st, p, r, s, f);
+hipError_t launch_cg_update_xp(void *x, void *p, const void *r, CgScalars *s, const double *rr_partial, int prow,
+                               const Counts &counts, double delta, const FieldShape &f, int prec, hipStream_t st) {
+  if (prec == 0) update_xp<double>(x, p, r, s, rr_partial, prow, counts, delta, f, st);
+  else update_xp<float>(x, p, r, s, rr_partial, prow, counts, delta, f, st);
   return hipGetLastError();
 }
 
@@ -370,10 +299,9 @@ hipError_t launch_residual(void *r, const void *b, const void *q, double *partia
 // After a (re)computation of r = b - A x in FP64: rho = ||r||^2.  With set_b2
 // the partial sums are those of b itself and only b2 / stop2 are set.
 // Otherwise rhs that are not finished are (re)activated: finished means
-// converged (rho <= stop2), broken down, or b = 0.  reset_p_mask != 0 marks
-// that p must be reset to r by the caller (first start).
+// converged (rho <= stop2), broken down, or b = 0. 
 __global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *partial, int nblk, double tol,
-                                                   int set_b2, int first) {
+                                                   int set_b2) {
   const int r = blockIdx.x;
   CgScalars &s = S[r];
   const double v = sum_partials(partial + (size_t)r * nblk, nblk);
@@ -383,17 +311,14 @@ __global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *p
     s.stop2 = tol * tol * v;
     s.iters = 0;
     s.status = 0;
-    s.active = 0;
+    s.active = s.act_it = 0;
     s.need_update = 0;
-    s.do_p = 0;
     s.rmax = 0.0;
     return;
   }
   s.rho = v;
-  s.rho64 = v;
   s.rmax = sqrt(v);
   s.need_update = 0;
-  if (first) s.beta = 0.0;
   if (s.status != 0) {
     s.active = 0;
     return;
@@ -407,8 +332,8 @@ __global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *p
 }
 
 hipError_t launch_cg_restart(CgScalars *s, const double *partial, int nblk, int nrhs, double tol, int set_b2,
-                             int first, hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_restart, dim3(nrhs), dim3(BT), 0, st, s, partial, nblk, tol, set_b2, first);
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_cg_restart, dim3(nrhs), dim3(BT), 0, st, s, partial, nblk, tol, set_b2);
   return hipGetLastError();
 }
 

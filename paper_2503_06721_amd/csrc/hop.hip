@@ -17,6 +17,8 @@
 //    one lane, coalesced across the 64 sites of the wavefront.  Register use
 //    no longer grows with d_R^2, which is what limits the site-parallel form
 //    for large representations.
+#include <type_traits>
+
 #include "wd_common.h"
 #include "wd_hop.h"
 #include "wd_kernels.h"
@@ -85,8 +87,9 @@ template <int D, bool REAL, typename T, bool DAG, bool NTL, int RL, int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k_hop_sp(HopArgs a) {
   using L = typename LinkT<T, REAL>::type;
   constexpr int TS = 256 / RL;   // sites per tile
+  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
   const int ngroups = a.ngroups;
-  const int w = tile_of_block(blockIdx.x, a.ntiles * ngroups, a.xcd_remap);
+  const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = w / ngroups, grp = w - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
@@ -122,8 +125,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
   const T cb = (T)(-0.5 * a.beta), ca = (T)a.alpha;
   double nrm = 0.0;
   // Two straight-line epilogues: every accumulator is used on both paths.
-  // The output and x_add are streamed (each element is touched once).
-  if (a.xadd) {
+  // The output and x_add are streamed (each element is touched once).  CG's
+  // last hop of an iteration updates the residual instead (wd_hop.h).
+  if (a.r) {
+    const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
+    cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase;
+    const double alpha = a.sc[sys0 + rk].alpha;
+    const bool act = a.sc[sys0 + rk].act_it != 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        const size_t o = (size_t)(s * D + c) * g.stride + i;
+        cplx<T> v = cb * acc[s][c];
+        const cplx<T> xv = ld_nt(xa + o);
+        v.re = fma(ca, xv.re, v.re);
+        v.im = fma(ca, xv.im, v.im);
+        const cplx<T> rn = cg_r_step(ld_nt(rf + o), v, alpha, act);
+        st_nt(rf + o, rn);
+        nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
+      }
+  } else if (a.xadd) {
     const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -468,8 +490,9 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
   // same XCD at nearly the same time: each link entry comes from HBM once
   // and from that XCD's L2 for the other groups.
   using L = typename LinkT<T, REAL>::type;
+  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
   const int ngroups = a.ngroups;
-  const int w = tile_of_block(blockIdx.x, a.ntiles * ngroups, a.xcd_remap);
+  const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = w / ngroups, grp = w - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
@@ -524,8 +547,29 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
   // Two straight-line epilogues (with and without x_add): every accumulator
   // is used on both paths, so no arithmetic is sunk behind a branch.  The
   // output and x_add are streamed (each element is touched once).
+  // CG's last hop of an iteration updates the residual instead (wd_hop.h).
   double nrm[NR];
-  if (a.xadd) {
+  if (a.r) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      nrm[k] = 0.0;
+      cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase + k * rstride;
+      const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase + k * rstride;
+      const double alpha = a.sc[sys0 + k].alpha;
+      const bool act = a.sc[sys0 + k].act_it != 0;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const size_t o = (size_t)(s * D + row) * g.stride + i;
+        cplx<T> v = cb * acc[k][s];
+        const cplx<T> xv = ld_nt(xa + o);
+        v.re = fma(ca, xv.re, v.re);
+        v.im = fma(ca, xv.im, v.im);
+        const cplx<T> rn = cg_r_step(ld_nt(rf + o), v, alpha, act);
+        st_nt(rf + o, rn);
+        nrm[k] += (double)rn.re * rn.re + (double)rn.im * rn.im;
+      }
+    }
+  } else if (a.xadd) {
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       nrm[k] = 0.0;
@@ -609,7 +653,7 @@ template <int D, bool REAL, typename T, bool DAG, int NR, bool NTL, int FLY>
 static hipError_t launch_cs2(const HopArgs &a, int stage, hipStream_t st) {
   constexpr int WU = cs_waves_form(D, sizeof(T) == 8, NR, false, FLY);
   constexpr int WP = cs_waves_form(D, sizeof(T) == 8, NR, true, FLY);
-  dim3 grid(a.ntiles * a.ngroups);
+  dim3 grid(a.ntiles * a.ngroups + a.lead);
   if constexpr (cs4_ok<D, T, NR, FLY>()) {
     // (d_R = 6 in FP32: one wave per SIMD fewer, so that it compiles without spills)
     constexpr int WQ = (D == 6 && sizeof(T) == 4) ? WP - 1 : WP;
@@ -652,16 +696,6 @@ static hipError_t launch_compact(const HopArgs &a0, int nrhs, int pair, int nr, 
   return launch_cs<D, false, T, DAG, 1, FLY>(a0, nrhs, pair ? 2 : 1, st, counts, prow);
 }
 
-template <int D, int FLY>
-static hipError_t compact_d(const HopArgs &a, int prec, int dagger, int nrhs, int pair, int nr, hipStream_t st,
-                            Counts *c, int *prow) {
-  if (prec == 0)
-    return dagger ? launch_compact<D, double, true, FLY>(a, nrhs, pair, nr, st, c, prow)
-                  : launch_compact<D, double, false, FLY>(a, nrhs, pair, nr, st, c, prow);
-  return dagger ? launch_compact<D, float, true, FLY>(a, nrhs, pair, nr, st, c, prow)
-                : launch_compact<D, float, false, FLY>(a, nrhs, pair, nr, st, c, prow);
-}
-
 template <int D, bool REAL, typename T, bool DAG>
 static hipError_t launch_typed(const HopArgs &a0, int nrhs, int variant, int nr, hipStream_t st, Counts *counts,
                                int *prow) {
@@ -672,7 +706,7 @@ static hipError_t launch_typed(const HopArgs &a0, int nrhs, int variant, int nr,
       const int rl = (nr == 4 && nrhs % 4 == 0) ? 4 : 1;
       set_tiles(a, 256 / rl, nrhs, counts, prow);
       a.ngroups = nrhs / rl;
-      dim3 grid(a.ntiles * a.ngroups);
+      dim3 grid(a.ntiles * a.ngroups + a.lead);
       constexpr int SW = sp_waves(D, sizeof(T) == 8);
       if (rl == 4) {
         if (a.ngroups == 1) hipLaunchKernelGGL((k_hop_sp<D, REAL, T, DAG, true, 4, SW>), grid, dim3(256), 0, st, a);
@@ -701,43 +735,75 @@ static hipError_t launch_typed(const HopArgs &a0, int nrhs, int variant, int nr,
   return launch_cs<D, REAL, T, DAG, 1>(a0, nrhs, stage, st, counts, prow);
 }
 
-template <int D, bool REAL>
-static hipError_t launch_d(const HopArgs &a, int prec, int dagger, int nrhs, int variant, int nr, hipStream_t st,
-                           Counts *c, int *prow) {
-  if (prec == 0)
-    return dagger ? launch_typed<D, REAL, double, true>(a, nrhs, variant, nr, st, c, prow)
-                  : launch_typed<D, REAL, double, false>(a, nrhs, variant, nr, st, c, prow);
-  return dagger ? launch_typed<D, REAL, float, true>(a, nrhs, variant, nr, st, c, prow)
-                : launch_typed<D, REAL, float, false>(a, nrhs, variant, nr, st, c, prow);
+// The kernels of one (precision, projector order, small or large d_R).  This
+// file is compiled in eight parts, WD_PART = 4 BIG + 2 (FP32) + DAG, each
+// holding one of these; part 0 also holds the dispatch.
+template <typename T, bool DAG, bool BIG>
+hipError_t hop_part(const HopArgs &a, int N, int rep, int d, int real, int nrhs, int variant, int nr, hipStream_t st,
+                    Counts *c, int *prow) {
+  if (variant == HOP_COMPACT || variant == HOP_COMPACT_PAIR) {
+    const int pair = variant == HOP_COMPACT_PAIR;
+    if constexpr (!BIG) {
+      if (rep == 2 && N == 2) return launch_compact<3, T, DAG, 2>(a, nrhs, pair, nr, st, c, prow);
+    } else {
+      if (rep == 2 && N == 3) return launch_compact<6, T, DAG, 2>(a, nrhs, pair, nr, st, c, prow);
+      if (rep == 2 && N == 4) return launch_compact<10, T, DAG, 2>(a, nrhs, pair, nr, st, c, prow);
+      if (rep == 3 && N == 4) return launch_compact<6, T, DAG, 3>(a, nrhs, pair, nr, st, c, prow);
+    }
+    return hipErrorInvalidValue;
+  }
+  if constexpr (!BIG) {
+    if (real && d == 3) return launch_typed<3, true, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (!real && d == 2) return launch_typed<2, false, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (!real && d == 3) return launch_typed<3, false, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (!real && d == 4) return launch_typed<4, false, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+  } else {
+    if (real && d == 8) return launch_typed<8, true, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (real && d == 15) return launch_typed<15, true, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (!real && d == 6) return launch_typed<6, false, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+    if (!real && d == 10) return launch_typed<10, false, T, DAG>(a, nrhs, variant, nr, st, c, prow);
+  }
+  return hipErrorInvalidValue;
 }
+
+#define WD_HOP_PART(T, DAG, BIG)                                                                              \
+  template hipError_t hop_part<T, DAG, BIG>(const HopArgs &, int, int, int, int, int, int, int, hipStream_t,     \
+                                            Counts *, int *)
+#if WD_PART == 1
+WD_HOP_PART(double, true, false);
+#elif WD_PART == 2
+WD_HOP_PART(float, false, false);
+#elif WD_PART == 3
+WD_HOP_PART(float, true, false);
+#elif WD_PART == 4
+WD_HOP_PART(double, false, true);
+#elif WD_PART == 5
+WD_HOP_PART(double, true, true);
+#elif WD_PART == 6
+WD_HOP_PART(float, false, true);
+#elif WD_PART == 7
+WD_HOP_PART(float, true, true);
+#else
+WD_HOP_PART(double, false, false);
+extern WD_HOP_PART(double, true, false);
+extern WD_HOP_PART(float, false, false);
+extern WD_HOP_PART(float, true, false);
+extern WD_HOP_PART(double, false, true);
+extern WD_HOP_PART(double, true, true);
+extern WD_HOP_PART(float, false, true);
+extern WD_HOP_PART(float, true, true);
 
 hipError_t launch_hop(const HopArgs &a, int N, int rep, int d, int real, int prec, int dagger, int nrhs, int variant,
                       int nr, hipStream_t st, Counts *counts, int *prow) {
   if (variant == HOP_MULTI) return launch_hop_mr(a, d, real, prec, dagger, nrhs, nr, st, counts, prow);
-  if (variant == HOP_COMPACT || variant == HOP_COMPACT_PAIR) {
-    const int pair = variant == HOP_COMPACT_PAIR;
-    if (rep == 2 && N == 2) return compact_d<3, 2>(a, prec, dagger, nrhs, pair, nr, st, counts, prow);
-    if (rep == 2 && N == 3) return compact_d<6, 2>(a, prec, dagger, nrhs, pair, nr, st, counts, prow);
-    if (rep == 2 && N == 4) return compact_d<10, 2>(a, prec, dagger, nrhs, pair, nr, st, counts, prow);
-    if (rep == 3 && N == 4) return compact_d<6, 3>(a, prec, dagger, nrhs, pair, nr, st, counts, prow);
-    return hipErrorInvalidValue;
-  }
-  if (real) {
-    switch (d) {
-      case 3: return launch_d<3, true>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 8: return launch_d<8, true>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 15: return launch_d<15, true>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-    }
-  } else {
-    switch (d) {
-      case 2: return launch_d<2, false>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 3: return launch_d<3, false>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 4: return launch_d<4, false>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 6: return launch_d<6, false>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-      case 10: return launch_d<10, false>(a, prec, dagger, nrhs, variant, nr, st, counts, prow);
-    }
-  }
-  return hipErrorInvalidValue;
+  const auto part = [&](auto t, auto big) {
+    using T = decltype(t);
+    constexpr bool BIG = decltype(big)::value;
+    return dagger ? hop_part<T, true, BIG>(a, N, rep, d, real, nrhs, variant, nr, st, counts, prow)
+                  : hop_part<T, false, BIG>(a, N, rep, d, real, nrhs, variant, nr, st, counts, prow);
+  };
+  if (prec == 0) return d >= 6 ? part(double{}, std::true_type{}) : part(double{}, std::false_type{});
+  return d >= 6 ? part(float{}, std::true_type{}) : part(float{}, std::false_type{});
 }
 
 bool hop_nr_supported(int N, int d, int prec, int variant, int nr) {
@@ -762,5 +828,6 @@ bool hop_variant_ok(int N, int rep, int d, int variant) {
   if (variant == HOP_COLOUR_QUAD) return d <= 6;
   return variant == HOP_COLOUR || variant == HOP_COLOUR_PAIR;
 }
+#endif
 
 }  // namespace wd

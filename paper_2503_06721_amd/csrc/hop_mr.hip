@@ -267,8 +267,9 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
   using L = typename LinkT<T, REAL>::type;
   constexpr int LPS = MrShape<D>::LPS, RPL = MrShape<D>::RPL, TS = MrShape<D>::TS;
   __shared__ L lbuf[2][MrTile<D, K>::NEP][TS];
+  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
   const int ngroups = a.ngroups;
-  const int wi = tile_of_block(blockIdx.x, a.ntiles * ngroups, a.xcd_remap);
+  const int wi = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = wi / ngroups, grp = wi - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
@@ -313,8 +314,26 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
   cplx<T> *out = static_cast<cplx<T> *>(a.out) + fbase;
   const uint32_t ooff = roff + (uint32_t)i;   // i < stride: lanes past the end write the padding
   double nrm = 0.0;
-  // two straight-line epilogues (see hop.hip); output and x_add streamed
-  if (a.xadd) {
+  // straight-line epilogues (see hop.hip); output and x_add streamed
+  if (a.r) {
+    const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
+    cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase;
+    const double alpha = a.sc[l * ngroups * K + r].alpha;
+    const bool act = a.sc[l * ngroups * K + r].act_it != 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int k = 0; k < RPL; ++k) {
+        const size_t row = (size_t)(s * D + k) * g.stride;
+        cplx<T> v = cb * acc[s][k];
+        const cplx<T> xv = ld_nt(at(xa + row, ooff));
+        v.re = fma(ca, xv.re, v.re);
+        v.im = fma(ca, xv.im, v.im);
+        const cplx<T> rn = cg_r_step(ld_nt(at(rf + row, ooff)), v, alpha, act);
+        st_nt(at(rf + row, ooff), rn);
+        nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
+      }
+  } else if (a.xadd) {
     const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -353,7 +372,7 @@ template <int D, bool REAL, typename T, bool DAG, int K>
 static hipError_t launch_mr_k(HopArgs a, int nrhs, hipStream_t st, Counts *counts, int *prow) {
   set_tiles(a, MrShape<D>::TS, nrhs, counts, prow);
   a.ngroups = nrhs / K;
-  dim3 grid(a.ntiles * a.ngroups);
+  dim3 grid(a.ntiles * a.ngroups + a.lead);
   constexpr int W = mr_waves(D, sizeof(T) == 8);
   if (a.ngroups == 1) hipLaunchKernelGGL((k_hop_mr<D, REAL, T, DAG, K, true, W>), grid, dim3(64 * K), 0, st, a);
   else hipLaunchKernelGGL((k_hop_mr<D, REAL, T, DAG, K, false, W>), grid, dim3(64 * K), 0, st, a);
@@ -373,28 +392,41 @@ static hipError_t launch_mr_t(const HopArgs &a, int nrhs, int nr, hipStream_t st
   return hipErrorInvalidValue;
 }
 
-template <int D, bool REAL>
-static hipError_t launch_mr_d(const HopArgs &a, int prec, int dagger, int nrhs, int nr, hipStream_t st, Counts *c,
-                              int *prow) {
-  if (prec == 0)
-    return dagger ? launch_mr_t<D, REAL, double, true>(a, nrhs, nr, st, c, prow)
-                  : launch_mr_t<D, REAL, double, false>(a, nrhs, nr, st, c, prow);
-  return dagger ? launch_mr_t<D, REAL, float, true>(a, nrhs, nr, st, c, prow)
-                : launch_mr_t<D, REAL, float, false>(a, nrhs, nr, st, c, prow);
+// The kernels of one (precision, projector order): this file is compiled in
+// four parts, WD_PART = 2 (FP32) + DAG; part 0 also holds the dispatch.
+template <typename T, bool DAG>
+hipError_t hop_mr_part(const HopArgs &a, int d, int real, int nrhs, int nr, hipStream_t st, Counts *c, int *prow) {
+  if (real && d == 3) return launch_mr_t<3, true, T, DAG>(a, nrhs, nr, st, c, prow);
+  if (!real && d == 3) return launch_mr_t<3, false, T, DAG>(a, nrhs, nr, st, c, prow);
+  if (!real && d == 6) return launch_mr_t<6, false, T, DAG>(a, nrhs, nr, st, c, prow);
+  return hipErrorInvalidValue;
 }
+
+#define WD_MR_PART(T, DAG) \
+  template hipError_t hop_mr_part<T, DAG>(const HopArgs &, int, int, int, int, hipStream_t, Counts *, int *)
+#if WD_PART == 1
+WD_MR_PART(double, true);
+#elif WD_PART == 2
+WD_MR_PART(float, false);
+#elif WD_PART == 3
+WD_MR_PART(float, true);
+#else
+WD_MR_PART(double, false);
+extern WD_MR_PART(double, true);
+extern WD_MR_PART(float, false);
+extern WD_MR_PART(float, true);
 
 bool hop_mr_ok(int d, int real) { return real ? d == 3 : (d == 3 || d == 6); }
 
 hipError_t launch_hop_mr(const HopArgs &a, int d, int real, int prec, int dagger, int nrhs, int nr, hipStream_t st,
                          Counts *counts, int *prow) {
   if (nr < 1 || nrhs % nr) return hipErrorInvalidValue;
-  if (real) {
-    if (d == 3) return launch_mr_d<3, true>(a, prec, dagger, nrhs, nr, st, counts, prow);
-  } else {
-    if (d == 3) return launch_mr_d<3, false>(a, prec, dagger, nrhs, nr, st, counts, prow);
-    if (d == 6) return launch_mr_d<6, false>(a, prec, dagger, nrhs, nr, st, counts, prow);
-  }
-  return hipErrorInvalidValue;
+  if (prec == 0)
+    return dagger ? hop_mr_part<double, true>(a, d, real, nrhs, nr, st, counts, prow)
+                  : hop_mr_part<double, false>(a, d, real, nrhs, nr, st, counts, prow);
+  return dagger ? hop_mr_part<float, true>(a, d, real, nrhs, nr, st, counts, prow)
+                : hop_mr_part<float, false>(a, d, real, nrhs, nr, st, counts, prow);
 }
+#endif
 
 }  // namespace wd

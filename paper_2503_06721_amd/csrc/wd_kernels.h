@@ -44,6 +44,33 @@ struct LatDesc {
   long long floff;  // offset of this lattice in the compact fundamental links, complex elements
 };
 
+// Number of valid partial sums per system (rows of a [system][prow] array).
+struct Counts {
+  int n[MAXSYS];
+};
+
+// CG (see api.hip for the algorithm).  One record per system.  rho, active,
+// iters, status, need_update and rmax are the state the host reads: written
+// by k_cg_restart and at the end of an iteration (cg_end_step).  rho_it and act_it
+// are their copies for the iteration under way (cg_alpha_step), read by every
+// block of the kernels that follow while the state is being rewritten.
+struct CgScalars {
+  double rho;       // <r, r>
+  double pAp;       // <p, A p> = ||D-hat p||^2
+  double alpha;     // step length of the iteration under way
+  double rho_it;    // <r, r> at its start
+  double rr;        // <r, r> at its end (k_cg_end)
+  double b2;        // ||b||^2
+  double stop2;     // tol^2 ||b||^2 (recursive-residual target)
+  double rmax;      // largest ||r|| since the last reliable update (mixed mode)
+  int active;       // 1 while iterating
+  int act_it;       // active at the start of the iteration under way, and no breakdown in it
+  int iters;
+  int status;       // wdirac_status
+  int need_update;  // residual replacement requested (mixed mode: reliable update)
+  int pad;
+};
+
 // Arguments of one hopping-term launch.  Pointers are device memory; fields
 // are packed half spinors, links the packed represented field.
 struct HopArgs {
@@ -62,11 +89,16 @@ struct HopArgs {
   int ntiles, ngroups;  // total tiles and rhs groups (set by the launcher)
   int tblock;           // t-blocked tile order (0 = lexicographic; single lattices only), see hop.hip
   int tiles_per_tx;     // set by the launcher
-};
-
-// Number of valid partial sums per system (rows of a [system][prow] array).
-struct Counts {
-  int n[MAXSYS];
+  // CG iterations (both need sc, one record per system):
+  CgScalars *sc;
+  // lead > 0: the first `lead` blocks (one per system) do the alpha step from
+  // the partial sums lp (rows of lprow, lcnt valid) while the others hop.
+  int lead, lprow;
+  const double *lp;
+  Counts lcnt;
+  // nullable: instead of storing out, r -= alpha_sys * out for the active
+  // systems; `partial` then receives the sums of |r|^2.
+  void *r;
 };
 
 // nr: right-hand sides per block of the colour-split form (1..4; reduced to
@@ -130,31 +162,10 @@ hipError_t launch_gamma5_axpy(void *out, const void *x, double c, const void *y,
 hipError_t launch_convert(void *out, int prec_out, const void *in, int prec_in, const FieldShape &f,
                           hipStream_t st);
 
-// CG (see api.hip for the algorithm).  One record per system.
-struct CgScalars {
-  double rho;       // <r, r>
-  double pAp;       // <p, A p> = ||D-hat p||^2
-  double alpha, beta;
-  double b2;        // ||b||^2
-  double stop2;     // tol^2 ||b||^2 (recursive-residual target)
-  double rmax;      // largest ||r|| since the last reliable update (mixed mode)
-  double rho64;     // FP64 residual norm^2 at the last reliable update (mixed mode)
-  int active;       // 1 while iterating
-  int iters;
-  int status;       // wdirac_status
-  int need_update;  // mixed mode: reliable update requested
-  int do_p;         // the last beta step ran for this system: p = r + beta p is due
-  int pad;
-};
-hipError_t launch_cg_alpha(CgScalars *s, const double *pAp_partial, int prow, const Counts &counts, int nsys,
-                           hipStream_t st);
-// x += alpha p (x in prec_x), r -= alpha q, partial |r|^2.  p, q, r in prec.
-hipError_t launch_cg_update_xr(void *x, int prec_x, void *r, const void *p, const void *q, const CgScalars *s,
-                               double *partial, const FieldShape &f, int prec, hipStream_t st);
-hipError_t launch_cg_beta(CgScalars *s, const double *rr_partial, int nblk, int nsys, double delta,
-                          hipStream_t st);
-hipError_t launch_cg_update_p(void *p, const void *r, const CgScalars *s, const FieldShape &f, int prec,
-                              hipStream_t st);
+// CG: x += alpha p and p = r + beta p, beta from the partial sums of |r|^2
+// (rows of prow); x, p, r in prec.  Also the state update of the iteration.
+hipError_t launch_cg_update_xp(void *x, void *p, const void *r, CgScalars *s, const double *rr_partial, int prow,
+                               const Counts &counts, double delta, const FieldShape &f, int prec, hipStream_t st);
 // r = b - q and partial |r|^2 (FP64)
 hipError_t launch_residual(void *r, const void *b, const void *q, double *partial, const FieldShape &f,
                            hipStream_t st);
@@ -162,7 +173,7 @@ hipError_t launch_residual(void *r, const void *b, const void *q, double *partia
 // rho = sum(partial) for a freshly computed FP64 residual, and every system
 // that is neither converged nor broken down is (re)activated.
 hipError_t launch_cg_restart(CgScalars *s, const double *partial, int nblk, int nsys, double tol, int set_b2,
-                             int first, hipStream_t st);
+                             hipStream_t st);
 // x64 += x32, then x32 = 0
 hipError_t launch_accum_x(void *x64, void *x32, const FieldShape &f, hipStream_t st);
 
