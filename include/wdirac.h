@@ -115,10 +115,13 @@ int wdirac_create_batch(wdirac_ctx **ctx, int Ng, int rep, const wdirac_geom *ge
 int wdirac_destroy(wdirac_ctx *ctx);
 
 /* Tuning options (host only; they change speed, never results beyond
- * rounding):
+ * rounding).  The launch shape of the hop (variant, rhs per block, XCD
+ * ranges, tile order) follows a rule on representation, precision, nrhs and
+ * size where nothing is set; once a variant is set, the others are 4, 1 and 0
+ * unless they are set too.
  *   WDIRAC_OPT_HOP_VARIANT_F64 / _F32  0 = one lane per site (d_R <= 6 only),
  *                                      1 = one wavefront per colour row of a
- *                                          64-site tile (default),
+ *                                          64-site tile,
  *                                      2 = as 1 with the forward and backward
  *                                          hop of each direction staged
  *                                          together (half the barriers),
@@ -136,13 +139,13 @@ int wdirac_destroy(wdirac_ctx *ctx);
  *                                          per block in LDS (complex d_R = 3
  *                                          and 6, real d_R = 3; 1, 2, 3, 4,
  *                                          6 or 12 rhs per block)
- *   WDIRAC_OPT_XCD_REMAP               1 (default) = give each XCD a
- *                                      contiguous range of site tiles
+ *   WDIRAC_OPT_XCD_REMAP               1 = give each XCD a contiguous range of
+ *                                      site tiles
  *   WDIRAC_OPT_CG_CHECK_EVERY          CG iterations between host checks of
  *                                      convergence (default 4, 1..1000)
  *   WDIRAC_OPT_MIXED_DELTA             reliable-update trigger of mixed CG,
  *                                      ||r|| < delta max ||r|| (default 0.01)
- *   WDIRAC_OPT_TILE_TBLOCK             0 (default) = site tiles in lexicographic
+ *   WDIRAC_OPT_TILE_TBLOCK             0 = site tiles in lexicographic
  *                                      order; b > 0 = in t-blocks of b slices
  *                                      (t-neighbours close in time), used
  *                                      when b divides T; b = -(10 bx + by) < 0

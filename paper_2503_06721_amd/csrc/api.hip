@@ -14,6 +14,8 @@
 #include "wd_common.h"
 #include "wd_kernels.h"
 
+constexpr int kAuto = -1000;
+
 struct wdirac_tuned {
   int valid, variant, nr, xcd_remap, tblock;
 };
@@ -24,6 +26,7 @@ struct wdirac_ctx {
   wd::Geom g[wd::MAXLAT];
   long long spre[wd::MAXLAT + 1];  // prefix sums of the packed row strides (sites)
   long long vpre[wd::MAXLAT + 1];  // prefix sums of the lattice volumes (canonical sites)
+  // hop launch shape options; kAuto where the caller has set none (auto_shape)
   int hop_variant[2];   // per precision (F64, F32): one of the wd::HOP_* forms
   int hop_nr[2];        // preferred right-hand sides per colour-split block
   wdirac_tuned tuned[2][13];   // autotuned shape per (precision, nrhs)
@@ -207,6 +210,98 @@ int effective_nr(const wdirac_ctx *c, int pref, int nrhs, int prec, int variant)
   return 1;
 }
 
+// Whether the 32-bit offsets of the multi-rhs form reach the whole lattice
+// (its largest: an entry of a (parity, direction) block of links, 16 bytes).
+bool hop_mr_reaches(const wdirac_ctx *c) {
+  for (int l = 0; l < c->nlat; ++l)
+    if ((long long)c->d * c->d * c->g[l].stride * 16 >= 1ll << 32) return false;
+  return true;
+}
+
+// Launch shape of a hop the caller has neither tuned nor set options for, by
+// representation, precision, right-hand sides and size (half-lattice sites
+// Vh).  Times are us per hop, the shape chosen against the colour-split form
+// with one hop per phase and up to four rhs per block, which served every call
+// before.
+//  * Two-index links, FP64: the compact form reads N^2 instead of d_R^2
+//    entries per link and rebuilds the others exactly as rep_links computes
+//    them (SU(3) SYM 24^4: 92 against 178, SU(4) 2AS 130 against 179, SU(4)
+//    SYM 188 against 397; 2AS below 16^4 is faster with stored links).  Not in
+//    FP32, where entries rebuilt from rounded links carry a larger error.
+//  * Several rhs at d_R = 6: one wavefront per rhs with the links staged per
+//    block, swept along t over sub-lattices so that neighbours stay in L2
+//    (SU(3) SYM 48x24^3, 12 rhs FP64: 1454 against 2004, FP32 836 against
+//    988).  SYM in FP64 below six rhs, or where no sweep fits, is faster one
+//    rhs per block in the compact form (24^4, 4 rhs: 303 against 350).
+//  * d_R <= 4, one rhs: two or four hops per phase, more loads in flight per
+//    barrier (SU(3) FUND 32^4 FP64: 135 against 155, FP32 79 against 86; 24^4:
+//    51.5 against 53.4; SU(2) FUND 16^4 7.8 against 9.0).  Several rhs in FP64:
+//    two hops per phase with two or three rhs per block (24^4, 12 rhs: SU(3)
+//    FUND 389 against 476, SU(2) ADJ 326 against 440); d_R = 4 on a large
+//    lattice gains only with 2 or 4 rhs (12: 556 against 529).
+//  * d_R = 15: fewer rhs per block, four spill (SU(4) ADJ 24^4 FP32, 12 rhs:
+//    1788 against 3083).
+//  * XCD ranges are left out where each would start a multiple of 256 KiB
+//    into every row and the fields outgrow the memory-side cache: the eight
+//    XCDs then stream the same HBM channels at the same time (SU(3) FUND FP64,
+//    32^4: 135 against 147 with ranges, 24x32^3: 103 against 115, 48x32^3: 206
+//    against 233; 24^4, whose ranges do not line up: 51.1 against 51.5; 16^4,
+//    in cache: 12.6 against 11.3), and for the stored links of d_R = 6, which
+//    nothing re-reads (SU(4) 2AS 48x24^3 FP32: 179 against 184).
+wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
+  const bool f64 = prec == WDIRAC_F64, even = nrhs % 2 == 0;
+  long long Vh = 0;
+  for (int l = 0; l < c->nlat; ++l) Vh += c->g[l].Vh;
+  const bool large = Vh >= 131072;
+  const int d = c->d;
+  wdirac_tuned s{1, wd::HOP_COLOUR, 4, 1, 0};
+  if (d == 6) {
+    // sweep of bx x-rows by by tiles of 32 sites of a (t, x) row
+    const wd::Geom &g = c->g[0];
+    const int nb = g.Y * g.Z % 64 == 0 ? g.Y * g.Z / 64 : 0;
+    const int bx = g.X % 3 == 0 ? 3 : g.X % 4 == 0 ? 4 : 2;
+    const int by = nb == 0 ? 0 : nb % 3 == 0 ? 3 : nb % 4 == 0 && (nb >= 8 || !f64) ? 4 : nb % 2 == 0 ? 2 : 0;
+    const bool sym = c->rep == WDIRAC_SYM, small = Vh < 75000;
+    const int nr = nrhs % 4 == 0 && (f64 || nrhs == 12 || !small) ? 4
+                   : nrhs % 3 == 0 && (f64 || !even || !small)    ? 3
+                   : even                                         ? 2
+                                                                  : 1;
+    const bool multi = nr > 1 && hop_mr_reaches(c) &&
+                       (!f64 ? large || nrhs >= 4 : sym ? nrhs >= 6 && by > 0 : nrhs >= 3);
+    if (multi) {
+      s.variant = wd::HOP_MULTI;
+      s.nr = nr;
+      s.tblock = by == 3 || (by && nrhs >= 6) ? -(10 * bx + by) : 0;
+    } else if (f64 && (sym || (nrhs == 1 && Vh >= 16384) || (nrhs == 2 && Vh >= 32768))) {
+      s.variant = wd::HOP_COMPACT;
+      s.nr = sym ? 1 : nrhs;
+    } else if (nrhs == 1 || (f64 && nrhs > 2)) {
+      s.variant = wd::HOP_COLOUR_PAIR;
+      s.nr = f64 && even ? 2 : 1;
+      if (!f64 && large && c->nlat == 1) s.xcd_remap = 0;
+    }
+  } else if (f64 && wd::compact_links_ok(c->N, c->rep)) {   // SYM, d_R = 3 and 10
+    s.variant = wd::HOP_COMPACT;
+    s.nr = d == 10 && even ? 2 : 1;
+  } else if (d <= 4 && nrhs == 1) {
+    s.variant = f64 ? (d == 2 && !large ? wd::HOP_COLOUR_PAIR : wd::HOP_COLOUR_QUAD)
+                    : (d == 3 && !c->real ? wd::HOP_COLOUR_PAIR : wd::HOP_COLOUR_QUAD);
+  } else if (f64 && (d == 2 || d == 3 || (d == 4 && (nrhs == 2 || nrhs == 4 || (!large && (nrhs < 6 || Vh >= 16384)))))) {
+    s.variant = wd::HOP_COLOUR_PAIR;
+    s.nr = d == 3 && nrhs % 3 == 0 && Vh >= 65536 ? 3 : even && (d == 4 || nrhs > 2 || !(c->real || d == 2)) ? 2 : 1;
+  } else if (d == 2 && even && Vh < 262144) {               // FP32
+    s.nr = 2;
+  } else if (d == 15) {
+    s.nr = f64 ? 1 : even ? 2 : 4;
+  } else if (nrhs == 1 || (f64 && (nrhs == 2 || nrhs == 4))) {   // ADJ d_R = 8; SYM d_R = 10 in FP32
+    s.variant = wd::HOP_COLOUR_PAIR;
+    s.nr = 1;
+  }
+  // (one rhs only: the rhs groups of a tile share its links in one XCD's L2)
+  if (c->nlat == 1 && nrhs == 1 && Vh >= 262144 && Vh % 131072 == 0 && (f64 || d < 15)) s.xcd_remap = 0;
+  return s;
+}
+
 // What a hop of a CG iteration does beside hopping (wd_kernels.h, HopArgs):
 // the alpha step from the partial sums lp, or the update of the residual r.
 struct CgHop {
@@ -223,14 +318,15 @@ struct CgHop {
 int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_parity, int dagger, int nrhs,
         double alpha, const void *xadd, double beta, int prec, double *partial, hipStream_t st,
         wd::Counts *counts = nullptr, int *prow = nullptr, const CgHop *cg = nullptr) {
-  int variant = c->hop_variant[prec], pref = c->hop_nr[prec], remap = c->xcd_remap, tblock = c->tblock;
-  const wdirac_tuned &tn = c->tuned[prec][nrhs];
-  if (tn.valid) {
-    variant = tn.variant;
-    pref = tn.nr;
-    remap = tn.xcd_remap;
-    tblock = tn.tblock;
+  wdirac_tuned sh = c->tuned[prec][nrhs];
+  if (!sh.valid) {
+    sh = auto_shape(c, prec, nrhs);
+    if (c->hop_variant[prec] != kAuto) sh = wdirac_tuned{1, c->hop_variant[prec], 4, 1, 0};
+    if (c->hop_nr[prec] != kAuto) sh.nr = c->hop_nr[prec];
+    if (c->xcd_remap != kAuto) sh.xcd_remap = c->xcd_remap;
+    if (c->tblock != kAuto) sh.tblock = c->tblock;
   }
+  if (sh.variant == wd::HOP_MULTI && !hop_mr_reaches(c)) sh.variant = wd::HOP_COLOUR;
   wd::HopArgs a;
   a.out = out;
   a.in = in;
@@ -246,12 +342,12 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
     a.lat[l].floff = (long long)8 * c->N * c->N * c->spre[l];
   }
   a.parity = out_parity;
-  a.xcd_remap = remap;
+  a.xcd_remap = sh.xcd_remap;
   a.alpha = alpha;
   a.beta = beta;
   a.partial = partial;
   a.prow = a.ntiles = a.ngroups = 0;
-  a.tblock = c->nlat == 1 ? tblock : 0;
+  a.tblock = c->nlat == 1 ? sh.tblock : 0;
   a.tiles_per_tx = 0;
   a.sc = cg ? cg->sc : nullptr;
   a.lead = cg ? cg->nsys : 0;
@@ -261,8 +357,8 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
   a.r = cg ? cg->r : nullptr;
   wd::Counts cnt{};
   int pr = 0;
-  WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, variant,
-                        effective_nr(c, pref, nrhs, prec, variant), st, &cnt, &pr));
+  WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, sh.variant,
+                        effective_nr(c, sh.nr, nrhs, prec, sh.variant), st, &cnt, &pr));
   if (counts) *counts = cnt;
   if (prow) *prow = pr;
   return WDIRAC_OK;
@@ -403,12 +499,9 @@ int wdirac_create_batch(wdirac_ctx **ctx, int Ng, int rep, const wdirac_geom *ge
     c->spre[l + 1] = c->spre[l] + g.stride;
     c->vpre[l + 1] = c->vpre[l] + V;
   }
-  c->hop_variant[0] = wd::HOP_COLOUR;
-  c->hop_variant[1] = wd::HOP_COLOUR;
-  c->hop_nr[0] = c->hop_nr[1] = 4;
+  c->hop_variant[0] = c->hop_variant[1] = c->hop_nr[0] = c->hop_nr[1] = kAuto;
   std::memset(c->tuned, 0, sizeof(c->tuned));
-  c->xcd_remap = 1;
-  c->tblock = 0;
+  c->xcd_remap = c->tblock = kAuto;
   c->cg_check_every = 4;
   c->mixed_delta = 0.01;
   c->cg_graph = 1;
