@@ -169,7 +169,8 @@ CgWork carve_cg(const wdirac_ctx *c, int nrhs, int mode, void *ws) {
 }
 
 struct MsWork {
-  void *r, *q, *t, *u, *v, *p;   // FP64 half fields; p holds nshift fields
+  void *r, *t, *u, *v, *p;   // FP64 half fields; r holds a ring of residuals, p nshift fields
+  int ring;                  // residuals kept: one where only the base shift needs them
   double *P1, *P2, *P3;
   wd::MsScalars *sc;
   size_t bytes;
@@ -179,7 +180,9 @@ MsWork carve_ms(const wdirac_ctx *c, int nshift, void *ws) {
   Carver cv{static_cast<char *>(ws)};
   MsWork w{};
   const size_t h = half_bytes(c, 1, WDIRAC_F64);
-  w.r = cv.take(h); w.q = cv.take(h); w.t = cv.take(h); w.u = cv.take(h); w.v = cv.take(h);
+  w.ring = nshift > 1 ? wd::MSRING : 1;
+  w.r = cv.take((size_t)w.ring * h);
+  w.t = cv.take(h); w.u = cv.take(h); w.v = cv.take(h);
   w.p = cv.take((size_t)nshift * h);
   w.P1 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
   w.P2 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
@@ -305,12 +308,17 @@ wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
 // What a hop of a CG iteration does beside hopping (wd_kernels.h, HopArgs):
 // the alpha step from the partial sums lp, or the update of the residual r.
 struct CgHop {
-  wd::CgScalars *sc;
-  int nsys;             // leading blocks of the alpha step (0: none)
-  const double *lp;
-  int lprow;
-  wd::Counts lcnt;
-  void *r;              // nullable
+  wd::CgScalars *sc = nullptr;
+  int lead = 0;         // leading blocks of the alpha step (0: none)
+  const double *lp = nullptr;
+  int lprow = 0;
+  wd::Counts lcnt{};
+  void *r = nullptr;    // r = rin - alpha (A p + sigma ps)
+  const void *rin = nullptr, *ps = nullptr;
+  double sigma = 0.0;
+  wd::MsScalars *ms = nullptr;
+  const double *lp2 = nullptr;
+  int lcnt2 = 0;
 };
 
 // One hopping-term launch over every lattice of the context.  counts/prow
@@ -349,12 +357,19 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
   a.prow = a.ntiles = a.ngroups = 0;
   a.tblock = c->nlat == 1 ? sh.tblock : 0;
   a.tiles_per_tx = 0;
-  a.sc = cg ? cg->sc : nullptr;
-  a.lead = cg ? cg->nsys : 0;
-  a.lp = cg ? cg->lp : nullptr;
-  a.lprow = cg ? cg->lprow : 0;
-  a.lcnt = cg ? cg->lcnt : wd::Counts{};
-  a.r = cg ? cg->r : nullptr;
+  const CgHop none, &h = cg ? *cg : none;
+  a.sc = h.sc;
+  a.ms = h.ms;
+  a.lead = h.lead;
+  a.lp = h.lp;
+  a.lprow = h.lprow;
+  a.lcnt = h.lcnt;
+  a.lp2 = h.lp2;
+  a.lcnt2 = h.lcnt2;
+  a.r = h.r;
+  a.rin = h.rin;
+  a.ps = h.ps;
+  a.sigma = h.sigma;
   wd::Counts cnt{};
   int pr = 0;
   WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, sh.variant,
@@ -1044,18 +1059,22 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
   int hop_count = 0, updates = 0;
 
   // b2, stop2
+  wd::Counts rcnt = wd::uniform_counts(nbb);   // partial sums of |r|^2 in w.P2: per system, and their row length
+  int rprow = nbb;
   WD_HIP(wd::launch_norm2_partial(w.P2, b, f, WDIRAC_F64, st));
-  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 1, st));
+  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, rprow, rcnt, ns, tol, 1, st));
   // r = b - A x (FP64)
   auto true_residual = [&]() -> int {
+    CgHop cr;
+    cr.r = w.r;
+    cr.rin = b;
     WD_TRY(dhat(ctx, w.u, x, UR64, m0, 0, nrhs, WDIRAC_F64, w.t, nullptr, st, nullptr, nullptr, clov64));
-    WD_TRY(dhat(ctx, w.q, w.u, UR64, m0, 1, nrhs, WDIRAC_F64, w.v, nullptr, st, nullptr, nullptr, clov64));
-    WD_HIP(wd::launch_residual(w.r, b, w.q, w.P2, f, st));
+    WD_TRY(dhat(ctx, w.q, w.u, UR64, m0, 1, nrhs, WDIRAC_F64, w.v, w.P2, st, &rcnt, &rprow, clov64, nullptr, &cr));
     hop_count += 4;
     return WDIRAC_OK;
   };
   WD_TRY(true_residual());
-  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, st));
+  WD_HIP(wd::launch_cg_restart(w.sc, w.P2, rprow, rcnt, ns, tol, 0, st));
   void *r = w.r, *p = w.p, *q = w.q, *t = w.t, *u = w.u, *v = w.v, *xi = x;
   const void *UR = UR64, *clov = clov64;
   int prec = WDIRAC_F64;
@@ -1092,7 +1111,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
       // residual replacement in FP64 (verifies convergence of the recursion)
       if (mixed) WD_HIP(wd::launch_accum_x(x, w.x32, f, st));
       WD_TRY(true_residual());
-      WD_HIP(wd::launch_cg_restart(w.sc, w.P2, nbb, ns, tol, 0, st));
+      WD_HIP(wd::launch_cg_restart(w.sc, w.P2, rprow, rcnt, ns, tol, 0, st));
       if (mixed) WD_HIP(wd::launch_convert(w.r32, WDIRAC_F32, w.r, WDIRAC_F64, f, st));
       ++updates;
       for (int k = 0; k < ns; ++k)
@@ -1113,7 +1132,14 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
         // first of its hops, r -= alpha A p in the second (A p itself is not
         // stored; q holds D_ee u of the clover form)
         WD_TRY(dhat(ctx, u, p, UR, m0, 0, nrhs, prec, t, w.P1, st, &cnt, &prow, clov));
-        const CgHop ca{w.sc, ns, w.P1, prow, cnt, nullptr}, cr{w.sc, 0, nullptr, 0, {}, r};
+        CgHop ca, cr;
+        ca.sc = cr.sc = w.sc;
+        ca.lead = ns;
+        ca.lp = w.P1;
+        ca.lprow = prow;
+        ca.lcnt = cnt;
+        cr.r = r;
+        cr.rin = r;
         WD_TRY(dhat(ctx, q, u, UR, m0, 1, nrhs, prec, v, w.P2, st, &cnt, &prow, clov, &ca, &cr));
         WD_HIP(wd::launch_cg_update_xp(xi, p, r, w.sc, w.P2, prow, cnt, delta, f, prec, st));
       }
@@ -1143,7 +1169,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
   if (mixed) WD_HIP(wd::launch_accum_x(x, w.x32, f, st));
   // final FP64 true residual of the returned x
   WD_TRY(true_residual());
-  WD_HIP(wd::launch_finalize_sum(w.P1, w.P2, nbb, wd::uniform_counts(nbb), ns, ns, st));
+  WD_HIP(wd::launch_finalize_sum(w.P1, w.P2, rprow, rcnt, ns, ns, st));
   std::vector<double> res2(ns);
   WD_HIP(hipMemcpyAsync(res2.data(), w.P1, ns * sizeof(double), hipMemcpyDeviceToHost, st));
   WD_HIP(hipMemcpyAsync(hs.data(), w.sc, ns * sizeof(wd::CgScalars), hipMemcpyDeviceToHost, st));
@@ -1287,7 +1313,7 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
   auto field = [&](void *base_ptr, int k) { return static_cast<void *>(static_cast<char *>(base_ptr) + (size_t)k * hb); };
   // x_k = 0 (padding included), p_k = b, r = b
   WD_HIP(hipMemsetAsync(x, 0, (size_t)nshift * hb, st));
-  WD_HIP(wd::launch_lincomb(w.r, 1.0, b, 0.0, nullptr, f, WDIRAC_F64, st));
+  WD_HIP(wd::launch_lincomb(field(w.r, w.ring - 1), 1.0, b, 0.0, nullptr, f, WDIRAC_F64, st));
   for (int k = 0; k < nshift; ++k) WD_HIP(wd::launch_lincomb(field(w.p, k), 1.0, b, 0.0, nullptr, f, WDIRAC_F64, st));
   WD_HIP(wd::launch_norm2_partial(w.P2, b, f, WDIRAC_F64, st));
   // the recursion stops at half the tolerance, leaving room for the drift of
@@ -1295,38 +1321,67 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
   WD_HIP(wd::launch_ms_init(w.sc, w.P2, nbb, dl, nshift, base, sigma0, 0.5 * tol, st));
   int hop_count = 0, rc = WDIRAC_OK;
   wd::MsScalars hs{};
-  void *pb = field(w.p, base);
+  void *pb = field(w.p, base), *xb = field(x, base);
+  // |p|^2 of the next step length (sigma0 > 0): at first that of b
+  const double *pp = w.P2;
+  int npp = nbb, slot = 0;
+  const auto flush = [&]() -> int {   // the other shifts' updates of the iterations in the ring
+    if (slot && nshift > 1)
+      WD_HIP(wd::launch_ms_update_xp(x, w.p, w.r, w.sc, fstride, f, slot, st));
+    slot = 0;
+    return WDIRAC_OK;
+  };
   for (;;) {
     WD_HIP(hipMemcpyAsync(&hs, w.sc, sizeof(hs), hipMemcpyDeviceToHost, st));
     WD_HIP(hipStreamSynchronize(st));
-    if (!hs.active) break;
-    if (hs.iters >= maxit) {
+    if (!hs.cg.active) break;
+    if (hs.cg.iters >= maxit) {
       rc = WDIRAC_ENOCONV;
       break;
     }
-    const int nit = std::min(ctx->cg_check_every, std::max(1, maxit - hs.iters));
+    const int nit = std::min(ctx->cg_check_every, std::max(1, maxit - hs.cg.iters));
     for (int it = 0; it < nit; ++it) {
       wd::Counts cnt{};
       int prow = 0;
       WD_TRY(dhat(ctx, w.u, pb, UR64, m0, 0, 1, WDIRAC_F64, w.t, w.P1, st, &cnt, &prow));
-      if (sigma0 != 0.0) WD_HIP(wd::launch_norm2_partial(w.P3, pb, f, WDIRAC_F64, st));
-      WD_TRY(dhat(ctx, w.q, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, nullptr, st));
-      if (sigma0 != 0.0) WD_HIP(wd::launch_lincomb(w.q, 1.0, w.q, sigma0, pb, f, WDIRAC_F64, st));
-      WD_HIP(wd::launch_ms_alpha(w.sc, w.P1, prow, cnt, sigma0 != 0.0 ? w.P3 : nullptr, nbb, st));
-      WD_HIP(wd::launch_ms_update_r(w.r, w.q, w.sc, w.P2, f, st));
-      WD_HIP(wd::launch_ms_beta(w.sc, w.P2, nbb, st));
-      WD_HIP(wd::launch_ms_update_xp(x, w.p, w.r, w.sc, fstride, f, nshift, st));
+      CgHop ca, cr;
+      ca.lead = 1;
+      ca.ms = w.sc;
+      ca.lp = w.P1;
+      ca.lprow = prow;
+      ca.lcnt = cnt;
+      cr.sc = &w.sc->cg;
+      cr.rin = field(w.r, (slot + w.ring - 1) % w.ring);
+      cr.r = field(w.r, slot % w.ring);
+      if (sigma0 != 0.0) {
+        ca.lp2 = pp;
+        ca.lcnt2 = npp;
+        cr.ps = pb;
+        cr.sigma = sigma0;
+      }
+      // (w.t is only the hop's nominal output: r is stored in its place)
+      WD_TRY(dhat(ctx, w.t, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, w.P2, st, &cnt, &prow, nullptr, &ca, &cr));
+      WD_HIP(wd::launch_ms_update_base(xb, pb, cr.r, w.sc, w.P2, cnt.n[0], slot, sigma0 != 0.0 ? w.P3 : nullptr, &npp,
+                                       f, st));
+      pp = w.P3;
+      if (++slot == wd::MSRING) WD_TRY(flush());
       hop_count += 4;
     }
   }
+  WD_TRY(flush());
   // true residuals ||b - (A + sigma_k) x_k||
   std::vector<double> res2(nshift);
   for (int k = 0; k < nshift; ++k) {
+    wd::Counts cnt{};
+    int prow = 0;
+    CgHop cr;
+    cr.r = w.r;
+    cr.rin = b;
+    cr.ps = field(x, k);
+    cr.sigma = shifts[k];
     WD_TRY(dhat(ctx, w.u, field(x, k), UR64, m0, 0, 1, WDIRAC_F64, w.t, nullptr, st));
-    WD_TRY(dhat(ctx, w.q, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, nullptr, st));
-    WD_HIP(wd::launch_lincomb(w.q, 1.0, w.q, shifts[k], field(x, k), f, WDIRAC_F64, st));
-    WD_HIP(wd::launch_residual(w.r, b, w.q, w.P2, f, st));
-    WD_HIP(wd::launch_finalize_sum(w.P1, w.P2, nbb, wd::uniform_counts(nbb), 1, 1, st));
+    WD_TRY(dhat(ctx, w.t, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, w.P2, st, &cnt, &prow, nullptr, nullptr, &cr));
+    WD_HIP(wd::launch_finalize_sum(w.P1, w.P2, prow, cnt, 1, 1, st));
     WD_HIP(hipMemcpyAsync(&res2[k], w.P1, sizeof(double), hipMemcpyDeviceToHost, st));
     hop_count += 4;
   }
@@ -1339,10 +1394,10 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
     sk.iters = hs.siters[k];
     sk.reliable_updates = 0;
     sk.hops = hop_count;
-    sk.true_rel_resid = hs.b2 > 0.0 ? std::sqrt(res2[k] / hs.b2) : 0.0;
+    sk.true_rel_resid = hs.cg.b2 > 0.0 ? std::sqrt(res2[k] / hs.cg.b2) : 0.0;
     sk.seconds = secs;
-    int stk = hs.status;
-    if (stk == WDIRAC_OK && hs.b2 > 0.0 && (hs.sact[k] || !(sk.true_rel_resid <= tol))) stk = WDIRAC_ENOCONV;
+    int stk = hs.cg.status;
+    if (stk == WDIRAC_OK && hs.cg.b2 > 0.0 && (hs.sact[k] || !(sk.true_rel_resid <= tol))) stk = WDIRAC_ENOCONV;
     sk.status = stk;
     if (stk == WDIRAC_EBREAKDOWN) worst = WDIRAC_EBREAKDOWN;
     else if (stk == WDIRAC_ENOCONV && worst == WDIRAC_OK) worst = WDIRAC_ENOCONV;

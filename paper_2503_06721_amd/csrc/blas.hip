@@ -271,40 +271,15 @@ hipError_t launch_cg_update_xp(void *x, void *p, const void *r, CgScalars *s, co
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(BT) void k_residual(void *r, const void *b, const void *q, double *partial,
-                                                 FieldShape f) {
-  __shared__ double sh[BT / 64];
-  const int i = blockIdx.x * BT + threadIdx.x, sy = blockIdx.y;
-  double nrm = 0.0;
-  if (i < f.vh[sy]) {
-    const size_t base = (size_t)f.off[sy] + i;
-    for (int c = 0; c < f.ncomp; ++c) {
-      const size_t o = base + (size_t)c * f.stride[sy];
-      const cplx<double> v = ld<double>(b, o) - ld<double>(q, o);
-      st<double>(r, o, v);
-      nrm += v.re * v.re + v.im * v.im;
-    }
-  }
-  nrm = block_sum(nrm, sh);
-  if (threadIdx.x == 0) partial[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = nrm;
-}
-
-hipError_t launch_residual(void *r, const void *b, const void *q, double *partial, const FieldShape &f,
-                           hipStream_t st) {
-  dim3 grid(blas_nblocks(f), f.nsys);
-  hipLaunchKernelGGL(k_residual, grid, dim3(BT), 0, st, r, b, q, partial, f);
-  return hipGetLastError();
-}
-
 // After a (re)computation of r = b - A x in FP64: rho = ||r||^2.  With set_b2
 // the partial sums are those of b itself and only b2 / stop2 are set.
 // Otherwise rhs that are not finished are (re)activated: finished means
 // converged (rho <= stop2), broken down, or b = 0. 
-__global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *partial, int nblk, double tol,
-                                                   int set_b2) {
+__global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *partial, int prow, Counts cnt,
+                                                   double tol, int set_b2) {
   const int r = blockIdx.x;
   CgScalars &s = S[r];
-  const double v = sum_partials(partial + (size_t)r * nblk, nblk);
+  const double v = sum_partials(partial + (size_t)r * prow, cnt.n[r]);
   if (threadIdx.x != 0) return;
   if (set_b2) {
     s.b2 = v;
@@ -331,9 +306,9 @@ __global__ __launch_bounds__(BT) void k_cg_restart(CgScalars *S, const double *p
   s.active = (s.b2 > 0.0 && v > s.stop2) ? 1 : 0;
 }
 
-hipError_t launch_cg_restart(CgScalars *s, const double *partial, int nblk, int nrhs, double tol, int set_b2,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_restart, dim3(nrhs), dim3(BT), 0, st, s, partial, nblk, tol, set_b2);
+hipError_t launch_cg_restart(CgScalars *s, const double *partial, int prow, const Counts &counts, int nsys, double tol,
+                             int set_b2, hipStream_t st) {
+  hipLaunchKernelGGL(k_cg_restart, dim3(nsys), dim3(BT), 0, st, s, partial, prow, counts, tol, set_b2);
   return hipGetLastError();
 }
 
@@ -394,32 +369,35 @@ hipError_t launch_gamma5_axpy(void *out, const void *x, double c, const void *y,
 //                                        + zeta_k^old a_old (1 + delta_k a)),
 //   alpha_k = a zeta_k' / zeta_k,   beta_k = b (zeta_k' / zeta_k)^2,
 //   x_k += alpha_k p_k,   p_k = zeta_k' r' + beta_k p_k.
+// The base shift has delta = 0 and zeta = 1 throughout.  Only its p feeds the
+// operator, so the updates of the other shifts wait until MSRING iterations
+// can be applied in one pass over x_k and p_k (launch_ms_update_xp), from the
+// residuals kept in a ring and the scalars kept per ring slot.
 __global__ void k_ms_init(MsScalars *S, const double *b2_partial, int nblk, ShiftList d, int nshift, int base,
                           double sigma0, double tol) {
   const double b2 = sum_partials(b2_partial, nblk);
   if (threadIdx.x != 0) return;
   MsScalars &s = *S;
-  s.b2 = b2;
-  s.stop2 = tol * tol * b2;
-  s.rr = b2;
-  s.pAp = 0.0;
-  s.alpha = 0.0;
+  s.cg.b2 = b2;
+  s.cg.stop2 = tol * tol * b2;
+  s.cg.rho = b2;
+  s.cg.pAp = 0.0;
+  s.cg.alpha = 0.0;
+  s.cg.act_it = s.cg.need_update = 0;
+  s.cg.iters = 0;
   s.alpha_old = 1.0;
-  s.beta = 0.0;
   s.beta_old = 0.0;
   s.sigma0 = sigma0;
-  s.iters = 0;
   s.nshift = nshift;
   s.base = base;
+  s.xb_it = 0;
   // a non-finite right-hand side is a breakdown, not a zero source
-  s.status = isfinite(b2) ? 0 : -5;
-  s.active = (b2 > 0.0 && isfinite(b2)) ? 1 : 0;
+  s.cg.status = isfinite(b2) ? 0 : -5;
+  s.cg.active = (b2 > 0.0 && isfinite(b2)) ? 1 : 0;
   for (int k = 0; k < MAXSHIFT; ++k) {
     s.delta[k] = k < nshift ? d.v[k] : 0.0;
     s.zeta[k] = s.zeta_old[k] = s.zeta_new[k] = 1.0;
-    s.as[k] = s.bs[k] = 0.0;
-    s.sact[k] = k < nshift ? s.active : 0;
-    s.upd[k] = 0;
+    s.sact[k] = k < nshift ? s.cg.active : 0;
     s.siters[k] = 0;
   }
 }
@@ -430,166 +408,173 @@ hipError_t launch_ms_init(MsScalars *s, const double *b2_partial, int nblk, cons
   return hipGetLastError();
 }
 
-// <p, (A + sigma0) p> = ||D-hat p||^2 + sigma0 ||p||^2, base step length and
-// the shifted step lengths.
-__global__ void k_ms_alpha(MsScalars *S, const double *uu, int prow, int cnt, const double *pp, int nblk_pp) {
-  MsScalars &s = *S;
-  const int act = s.active;
+// Scalars of every shift at the end of an iteration (one block, a thread per
+// shift): beta_k, rotation of the zeta history, convergence of each shift
+// (|zeta_k| ||r|| <= tol ||b||: its update of this iteration is its last), and
+// the ring slot's coefficients.  The base recursion runs while any shift is
+// still being updated.
+__device__ __forceinline__ void ms_end_step(MsScalars &s, double rr, int slot) {
+  const int k = threadIdx.x;
+  const int act = s.cg.act_it;
+  const bool ok = act && isfinite(rr);
+  const double b = rr / s.cg.rho_it, stop2 = s.cg.stop2;
+  __shared__ int any;
+  if (k == 0) any = 0;
   __syncthreads();
-  // the x updates flagged by the previous iteration's beta step are done:
-  // iterations launched after convergence must not repeat them
-  if (threadIdx.x == 0)
-    for (int k = 0; k < MAXSHIFT; ++k) s.upd[k] = 0;
-  if (!act) return;
-  double pAp = sum_partials(uu, cnt);
-  if (pp) {
-    const double p2 = sum_partials(pp, nblk_pp);
-    pAp += s.sigma0 * p2;
+  if (k < s.nshift) {
+    const int on = s.sact[k];
+    int upd = 0;
+    if (ok && on) {
+      const double z = s.zeta[k], zn = s.zeta_new[k], q = zn / z;
+      s.as[slot][k] = s.cg.alpha * zn / z;
+      s.bs[slot][k] = b * q * q;
+      s.zr[slot][k] = zn;
+      s.zeta_old[k] = z;
+      s.zeta[k] = zn;
+      s.siters[k] += 1;
+      const bool more = zn * zn * rr > stop2;
+      if (!more) s.sact[k] = 0;
+      else any = 1;
+      upd = more ? 3 : 1;
+    } else if (act && !ok) {
+      s.sact[k] = 0;
+    }
+    s.upd[slot][k] = upd;
   }
-  (void)prow;
-  if (threadIdx.x != 0) return;
-  s.pAp = pAp;
-  if (!(pAp > 0.0) || !isfinite(pAp)) {
-    s.status = -5;
-    s.active = 0;
-    for (int k = 0; k < s.nshift; ++k) s.sact[k] = s.upd[k] = 0;
+  __syncthreads();
+  if (k != 0 || !act) return;
+  s.cg.iters += 1;
+  if (!ok) {
+    s.cg.status = -5;
+    s.cg.active = 0;
     return;
   }
-  const double a = s.rr / pAp;
-  s.alpha = a;
-  for (int k = 0; k < s.nshift; ++k) {
-    if (!s.sact[k]) continue;
-    const double z = s.zeta[k], zo = s.zeta_old[k];
-    const double den = a * s.beta_old * (zo - z) + zo * s.alpha_old * (1.0 + s.delta[k] * a);
-    const double zn = z * zo * s.alpha_old / den;
-    s.zeta_new[k] = zn;
-    s.as[k] = a * zn / z;
-  }
+  s.alpha_old = s.cg.alpha;
+  s.beta_old = b;
+  s.cg.rho = rr;
+  s.cg.active = any;
 }
 
-hipError_t launch_ms_alpha(MsScalars *s, const double *uu_partial, int prow, const Counts &counts,
-                           const double *pp_partial, int nblk_pp, hipStream_t st) {
-  hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(BT), 0, st, s, uu_partial, prow, counts.n[0], pp_partial, nblk_pp);
-  return hipGetLastError();
-}
-
-// r -= alpha q (FP64), per-block partial sums of |r|^2.
-__global__ __launch_bounds__(BT) void k_ms_update_r(void *r, const void *q, const MsScalars *S, double *partial,
-                                                    FieldShape f) {
+// Base shift: x += alpha p, p = r + beta p as k_cg_update_xp (OWN), the first
+// block also advancing the scalars of every shift (whose fields no other block
+// reads), and |p|^2 summed on the way where the next step length needs it
+// (sigma0 > 0), which saves a pass over p.
+__global__ __launch_bounds__(BT) void k_ms_update_base(cplx<double> *__restrict__ x, cplx<double> *__restrict__ p,
+                                                       const cplx<double> *__restrict__ r, MsScalars *S,
+                                                       const double *__restrict__ rr_partial, int cnt, int slot,
+                                                       double *__restrict__ pp, int per, FieldShape f) {
   __shared__ double sh[BT / 64];
-  if (!S->active) return;
-  const double a = S->alpha;
+  MsScalars &s = *S;
+  const int act = s.cg.act_it, xb = s.xb_it;
+  const double a = s.cg.alpha, rho = s.cg.rho_it;
+  const double rr = act ? sum_partials(rr_partial, cnt) : 0.0;
+  if (blockIdx.x == 0 && blockIdx.y == 0) ms_end_step(s, rr, slot);
+  if (!act) return;
+  const bool ok = isfinite(rr);
+  const double b = rr / rho;
   const int i = blockIdx.x * BT + threadIdx.x;
-  double nrm = 0.0;
-  if (i < f.vh[0]) {
-    const size_t base = (size_t)f.off[0] + i;
-    for (int c = 0; c < f.ncomp; ++c) {
-      const size_t o = base + (size_t)c * f.stride[0];
-      const cplx<double> qv = ld<double>(q, o);
-      cplx<double> rv = ld<double>(r, o);
-      rv.re = fma(-a, qv.re, rv.re);
-      rv.im = fma(-a, qv.im, rv.im);
-      static_cast<cplx<double> *>(r)[o] = rv;
-      nrm += rv.re * rv.re + rv.im * rv.im;
+  double n = 0.0;
+  if (ok && i < f.vh[0]) {
+    const size_t st = f.stride[0];
+    const size_t base = (size_t)f.off[0] + i + (size_t)blockIdx.y * per * st;
+    for (int c = 0; c < per; c += 4) {
+      cplx<double> pv[4], xv[4], rv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const size_t o = base + (size_t)(c + k) * st;
+        pv[k] = p[o];
+        xv[k] = x[o];
+        rv[k] = r[o];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const size_t o = base + (size_t)(c + k) * st;
+        if (xb) x[o] = mk(fma(a, pv[k].re, xv[k].re), fma(a, pv[k].im, xv[k].im));
+        const cplx<double> pn = mk(fma(b, pv[k].re, rv[k].re), fma(b, pv[k].im, rv[k].im));
+        p[o] = pn;
+        n += pn.re * pn.re + pn.im * pn.im;
+      }
     }
   }
-  nrm = block_sum(nrm, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = nrm;
+  if (pp) {
+    n = block_sum(n, sh);
+    if (threadIdx.x == 0) pp[blockIdx.y * gridDim.x + blockIdx.x] = n;
+  }
 }
 
-hipError_t launch_ms_update_r(void *r, const void *q, const MsScalars *s, double *partial, const FieldShape &f,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_ms_update_r, dim3(blas_nblocks(f)), dim3(BT), 0, st, r, q, s, partial, f);
+hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, const double *rr_partial, int cnt,
+                                 int slot, double *pp, int *npp, const FieldShape &f, hipStream_t st) {
+  const int nb = blas_nblocks(f);
+  const int per = nb >= 1024 ? f.ncomp : 4;
+  const dim3 grid(nb, f.ncomp / per);
+  *npp = nb * (f.ncomp / per);
+  hipLaunchKernelGGL(k_ms_update_base, grid, dim3(BT), 0, st, (cplx<double> *)x, (cplx<double> *)p,
+                     (const cplx<double> *)r, s, rr_partial, cnt, slot, pp, per, f);
   return hipGetLastError();
 }
 
-// beta, the shifted beta_k, rotation of the zeta history, and convergence of
-// each shift (|zeta_k| ||r|| <= tol ||b||: its update of this iteration is its
-// last).  The base recursion runs while any shift is still being updated.
-__global__ void k_ms_beta(MsScalars *S, const double *rr_partial, int nblk) {
-  MsScalars &s = *S;
-  if (!s.active) return;
-  const double rr = sum_partials(rr_partial, nblk);
-  if (threadIdx.x != 0) return;
-  s.iters += 1;
-  if (!isfinite(rr)) {
-    s.status = -5;
-    s.active = 0;
-    for (int k = 0; k < s.nshift; ++k) s.sact[k] = s.upd[k] = 0;
-    return;
-  }
-  const double b = rr / s.rr;
-  int any = 0;
-  for (int k = 0; k < s.nshift; ++k) {
-    s.upd[k] = s.sact[k];
-    if (!s.sact[k]) continue;
-    const double q = s.zeta_new[k] / s.zeta[k];
-    s.bs[k] = b * q * q;
-    s.siters[k] += 1;
-    s.zeta_old[k] = s.zeta[k];
-    s.zeta[k] = s.zeta_new[k];
-    if (s.zeta[k] * s.zeta[k] * rr <= s.stop2) s.sact[k] = 0;
-    any |= s.sact[k];
-  }
-  s.alpha_old = s.alpha;
-  s.beta_old = b;
-  s.beta = b;
-  s.rr = rr;
-  s.active = any;
-}
-
-hipError_t launch_ms_beta(MsScalars *s, const double *rr_partial, int nblk, hipStream_t st) {
-  hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(BT), 0, st, s, rr_partial, nblk);
-  return hipGetLastError();
-}
-
-// x_k += alpha_k p_k (shifts whose x update is due) and p_k = zeta_k r +
-// beta_k p_k (shifts still active; the base shift while any is), one thread
-// per site with the shifts in the inner loop, so that r is read once for all
-// of them (per shift 4 half-field passes instead of 5).  Shift fields are
-// `fstride` complex elements apart.
-__global__ __launch_bounds__(BT) void k_ms_update_xp(void *__restrict__ x, void *__restrict__ p,
-                                                     const void *__restrict__ r, const MsScalars *__restrict__ S,
-                                                     long long fstride, FieldShape f) {
+// The other shifts, N iterations at once: for every slot j in turn
+// x_k += as_jk p_k and p_k = zr_jk r_j + bs_jk p_k, where due.  Bound by memory:
+// 4 half fields per shift and N residuals, against 4 N per shift when every
+// iteration updates them (SU(3) FUND 32x24^3, 12 shifts: 342 us an iteration
+// before, 368 us in eight iterations now).  One thread per site with the
+// shifts in an inner loop, so that each residual is read once for all of them.
+template <int N>
+__global__ __launch_bounds__(BT) void k_ms_update_xp(cplx<double> *__restrict__ x, cplx<double> *__restrict__ p,
+                                                     const cplx<double> *__restrict__ ring,
+                                                     const MsScalars *__restrict__ S, long long fstride,
+                                                     FieldShape f) {
   const MsScalars &s = *S;
   const int i = blockIdx.x * BT + threadIdx.x;
   if (i >= f.vh[0]) return;
-  const int ns = s.nshift, kb = s.base, bact = s.active;
-  cplx<double> *xs = static_cast<cplx<double> *>(x);
-  cplx<double> *ps = static_cast<cplx<double> *>(p);
-  const cplx<double> *rr = static_cast<const cplx<double> *>(r);
-  const size_t base = (size_t)f.off[0] + i;
-  for (int c = 0; c < f.ncomp; ++c) {
-    const size_t o = base + (size_t)c * f.stride[0];
-    const cplx<double> rv = rr[o];
-    for (int k = 0; k < ns; ++k) {
-      const bool ux = s.upd[k] != 0;
-      const bool upd_p = k == kb ? bact != 0 : s.sact[k] != 0;
-      if (!ux && !upd_p) continue;   // uniform over the grid
-      const size_t ok = (size_t)k * fstride + o;
-      const cplx<double> pv = ps[ok];
-      if (ux) {
-        const double a = s.as[k];
-        cplx<double> xv = xs[ok];
+  const int ns = s.nshift, kb = s.base;
+  const size_t o = (size_t)f.off[0] + i + (size_t)blockIdx.y * f.stride[0];
+  cplx<double> r[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) r[j] = ring[(size_t)j * fstride + o];
+  for (int k = 0; k < ns; ++k) {
+    if (k == kb || !s.upd[0][k]) continue;   // uniform over the grid; once off, off in the later slots
+    const size_t ok = (size_t)k * fstride + o;
+    cplx<double> pv = p[ok], xv = x[ok];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int u = s.upd[j][k];
+      if (u & 1) {
+        const double a = s.as[j][k];
         xv.re = fma(a, pv.re, xv.re);
         xv.im = fma(a, pv.im, xv.im);
-        xs[ok] = xv;
       }
-      if (upd_p) {
-        const double z = s.zeta[k], b = s.bs[k];
-        cplx<double> pn;
-        pn.re = fma(z, rv.re, b * pv.re);
-        pn.im = fma(z, rv.im, b * pv.im);
-        ps[ok] = pn;
+      if (u & 2) {
+        const double z = s.zr[j][k], b = s.bs[j][k];
+        pv.re = fma(z, r[j].re, b * pv.re);
+        pv.im = fma(z, r[j].im, b * pv.im);
       }
     }
+    x[ok] = xv;
+    p[ok] = pv;
   }
 }
 
-hipError_t launch_ms_update_xp(void *x, void *p, const void *r, const MsScalars *s, long long fstride,
-                               const FieldShape &f, int, hipStream_t st) {
-  hipLaunchKernelGGL(k_ms_update_xp, dim3(blas_nblocks(f)), dim3(BT), 0, st, x, p, r, s, fstride, f);
-  return hipGetLastError();
+hipError_t launch_ms_update_xp(void *x, void *p, const void *ring, const MsScalars *s, long long fstride,
+                               const FieldShape &f, int n, hipStream_t st) {
+  const dim3 grid(blas_nblocks(f), f.ncomp);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(BT), 0, st, (cplx<double> *)x, (cplx<double> *)p, (const cplx<double> *)ring,
+                       s, fstride, f);
+    return hipGetLastError();
+  };
+  static_assert(MSRING == 8, "one instance per number of iterations");
+  switch (n) {
+    case 1: return go(k_ms_update_xp<1>);
+    case 2: return go(k_ms_update_xp<2>);
+    case 3: return go(k_ms_update_xp<3>);
+    case 4: return go(k_ms_update_xp<4>);
+    case 5: return go(k_ms_update_xp<5>);
+    case 6: return go(k_ms_update_xp<6>);
+    case 7: return go(k_ms_update_xp<7>);
+    case 8: return go(k_ms_update_xp<8>);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace wd

@@ -87,7 +87,7 @@ template <int D, bool REAL, typename T, bool DAG, bool NTL, int RL, int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k_hop_sp(HopArgs a) {
   using L = typename LinkT<T, REAL>::type;
   constexpr int TS = 256 / RL;   // sites per tile
-  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
+  if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = w / ngroups, grp = w - q * ngroups;
@@ -125,13 +125,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
   const T cb = (T)(-0.5 * a.beta), ca = (T)a.alpha;
   double nrm = 0.0;
   // Two straight-line epilogues: every accumulator is used on both paths.
-  // The output and x_add are streamed (each element is touched once).  CG's
-  // last hop of an iteration updates the residual instead (wd_hop.h).
+  // The output and x_add are streamed (each element is touched once).  A solver's
+  // residual is updated instead where r is given (wd_hop.h).
   if (a.r) {
     const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
     cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase;
-    const double alpha = a.sc[sys0 + rk].alpha;
-    const bool act = a.sc[sys0 + rk].act_it != 0;
+    const cplx<T> *ri = static_cast<const cplx<T> *>(a.rin) + fbase, *ps = static_cast<const cplx<T> *>(a.ps) + fbase;
+    const RStep<T> step(a, sys0 + rk);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
         const cplx<T> xv = ld_nt(xa + o);
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = cg_r_step(ld_nt(rf + o), v, alpha, act);
-        st_nt(rf + o, rn);
+        const cplx<T> rn = step(rf + o, ri + o, ps + o, v);
         nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
   } else if (a.xadd) {
@@ -490,7 +489,7 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
   // same XCD at nearly the same time: each link entry comes from HBM once
   // and from that XCD's L2 for the other groups.
   using L = typename LinkT<T, REAL>::type;
-  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
+  if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = w / ngroups, grp = w - q * ngroups;
@@ -547,16 +546,17 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
   // Two straight-line epilogues (with and without x_add): every accumulator
   // is used on both paths, so no arithmetic is sunk behind a branch.  The
   // output and x_add are streamed (each element is touched once).
-  // CG's last hop of an iteration updates the residual instead (wd_hop.h).
+  // A solver's residual is updated instead where r is given (wd_hop.h).
   double nrm[NR];
   if (a.r) {
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       nrm[k] = 0.0;
       cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase + k * rstride;
+      const cplx<T> *ri = static_cast<const cplx<T> *>(a.rin) + fbase + k * rstride;
+      const cplx<T> *ps = static_cast<const cplx<T> *>(a.ps) + fbase + k * rstride;
       const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase + k * rstride;
-      const double alpha = a.sc[sys0 + k].alpha;
-      const bool act = a.sc[sys0 + k].act_it != 0;
+      const RStep<T> step(a, sys0 + k);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const size_t o = (size_t)(s * D + row) * g.stride + i;
@@ -564,8 +564,7 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
         const cplx<T> xv = ld_nt(xa + o);
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = cg_r_step(ld_nt(rf + o), v, alpha, act);
-        st_nt(rf + o, rn);
+        const cplx<T> rn = step(rf + o, ri + o, ps + o, v);
         nrm[k] += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
     }

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
   using L = typename LinkT<T, REAL>::type;
   constexpr int LPS = MrShape<D>::LPS, RPL = MrShape<D>::RPL, TS = MrShape<D>::TS;
   __shared__ L lbuf[2][MrTile<D, K>::NEP][TS];
-  if ((int)blockIdx.x < a.lead) return cg_alpha_step(a);
+  if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int wi = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
   const int q = wi / ngroups, grp = wi - q * ngroups;
@@ -318,8 +318,8 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
   if (a.r) {
     const cplx<T> *xa = static_cast<const cplx<T> *>(a.xadd) + fbase;
     cplx<T> *rf = static_cast<cplx<T> *>(a.r) + fbase;
-    const double alpha = a.sc[l * ngroups * K + r].alpha;
-    const bool act = a.sc[l * ngroups * K + r].act_it != 0;
+    const cplx<T> *ri = static_cast<const cplx<T> *>(a.rin) + fbase, *ps = static_cast<const cplx<T> *>(a.ps) + fbase;
+    const RStep<T> step(a, l * ngroups * K + r);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -329,8 +329,7 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
         const cplx<T> xv = ld_nt(at(xa + row, ooff));
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = cg_r_step(ld_nt(at(rf + row, ooff)), v, alpha, act);
-        st_nt(at(rf + row, ooff), rn);
+        const cplx<T> rn = step(at(rf + row, ooff), at(ri + row, ooff), at(ps + row, ooff), v);
         nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
   } else if (a.xadd) {

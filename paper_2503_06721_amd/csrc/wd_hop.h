@@ -107,14 +107,70 @@ __device__ __forceinline__ void cg_alpha_step(const HopArgs &a) {
   }
 }
 
-// Residual update of one element in the epilogue of an iteration's last hop:
-// v = (A p) there, r -= alpha v in FP64, rounded to T as stored.  Returns the
-// stored value; an inactive system keeps its r.
-template <typename T>
-__device__ __forceinline__ cplx<T> cg_r_step(cplx<T> r, cplx<T> v, double alpha, bool act) {
-  const cplx<T> n = mk<T>((T)fma(-alpha, (double)v.re, (double)r.re), (T)fma(-alpha, (double)v.im, (double)r.im));
-  return act ? n : r;
+// The same for the multi-shift recursion (blas.hip): <p, (A + sigma0) p> and
+// the shifted zeta_k and alpha_k, a lane per shift.
+__device__ __forceinline__ void ms_alpha_step(const HopArgs &a) {
+  MsScalars &s = *a.ms;
+  const int act = s.cg.active;
+  double pAp = 0.0;
+  if (act) {
+    pAp = sum_partials(a.lp, a.lcnt.n[0]);
+    if (a.lp2) pAp += s.sigma0 * sum_partials(a.lp2, a.lcnt2);
+  }
+  const bool ok = act && pAp > 0.0 && isfinite(pAp);
+  const double al = s.cg.rho / pAp;
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (ok && k < s.nshift && s.sact[k]) {
+    const double z = s.zeta[k], zo = s.zeta_old[k];
+    const double den = al * s.beta_old * (zo - z) + zo * s.alpha_old * (1.0 + s.delta[k] * al);
+    s.zeta_new[k] = z * zo * s.alpha_old / den;
+  }
+  if (act && !ok && k < s.nshift) s.sact[k] = 0;
+  if (k != 0) return;
+  s.cg.act_it = ok;
+  s.cg.rho_it = s.cg.rho;
+  if (!act) return;
+  s.cg.pAp = pAp;
+  if (!ok) {
+    s.cg.status = -5;
+    s.cg.active = 0;
+    s.cg.alpha = 0.0;
+  } else {
+    s.xb_it = s.sact[s.base];
+    s.cg.alpha = al;
+  }
 }
+
+__device__ __forceinline__ void hop_lead(const HopArgs &a) {
+  if (a.ms) ms_alpha_step(a);
+  else cg_alpha_step(a);
+}
+
+// Residual update in the epilogue of a hop (HopArgs::r), element by element:
+// v = (A p) there, r = rin - alpha (v + sigma ps) in FP64, rounded to T as
+// stored.  Returns the stored value; an inactive system keeps rin.
+template <typename T>
+struct RStep {
+  double alpha, sigma;
+  bool act, shifted;
+  __device__ __forceinline__ RStep(const HopArgs &a, int sys)
+      : alpha(a.sc ? a.sc[sys].alpha : 1.0), sigma(a.sigma), act(a.sc ? a.sc[sys].act_it != 0 : true),
+        shifted(a.ps != nullptr) {}
+  __device__ __forceinline__ cplx<T> operator()(cplx<T> *r, const cplx<T> *rin, const cplx<T> *ps, cplx<T> v) const {
+    double re = v.re, im = v.im;
+    if (shifted) {
+      const cplx<T> q = ld_nt(ps);
+      re = fma(sigma, (double)q.re, re);
+      im = fma(sigma, (double)q.im, im);
+    }
+    const cplx<T> o = ld_nt(rin);
+    const cplx<T> n = mk<T>((T)fma(-alpha, re, (double)o.re), (T)fma(-alpha, im, (double)o.im));
+    const cplx<T> w = act ? n : o;
+    st_nt(r, w);
+    return w;
+  }
+};
 
 // Tile bookkeeping of a launch with tiles of ts sites: per-lattice tile
 // ranges, the partial-sum row length and counts, and the t-blocked or

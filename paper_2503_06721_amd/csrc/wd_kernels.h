@@ -71,6 +71,31 @@ struct CgScalars {
   int pad;
 };
 
+// Multi-shift CG (see blas.hip for the recurrences).  One system (one rhs of
+// a single lattice); shift k's fields are `fstride` complex elements apart.
+constexpr int MAXSHIFT = 32;
+// Iterations whose updates of x_k and p_k (k not the base shift) are applied
+// together, from as many residuals kept in a ring.
+constexpr int MSRING = 8;
+struct ShiftList {
+  double v[MAXSHIFT];
+};
+struct MsScalars {
+  CgScalars cg;       // base recursion (rho, pAp, alpha, active, act_it, iters, status; the rest unused)
+  double alpha_old, beta_old;
+  double sigma0;      // base (smallest) shift
+  int nshift, base;
+  int xb_it;          // the base shift's x is due in the iteration under way
+  int pad;
+  double delta[MAXSHIFT];   // sigma_k - sigma0
+  double zeta[MAXSHIFT], zeta_old[MAXSHIFT], zeta_new[MAXSHIFT];
+  int sact[MAXSHIFT];     // shift k is still updated
+  int siters[MAXSHIFT];   // iterations that updated shift k
+  // per ring slot: x_k += as p_k where upd & 1, then p_k = zr r + bs p_k where upd & 2
+  double as[MSRING][MAXSHIFT], zr[MSRING][MAXSHIFT], bs[MSRING][MAXSHIFT];
+  int upd[MSRING][MAXSHIFT];
+};
+
 // Arguments of one hopping-term launch.  Pointers are device memory; fields
 // are packed half spinors, links the packed represented field.
 struct HopArgs {
@@ -89,16 +114,22 @@ struct HopArgs {
   int ntiles, ngroups;  // total tiles and rhs groups (set by the launcher)
   int tblock;           // t-blocked tile order (0 = lexicographic; single lattices only), see hop.hip
   int tiles_per_tx;     // set by the launcher
-  // CG iterations (both need sc, one record per system):
+  // CG iterations.  lead > 0: the first `lead` blocks (one per system) do the
+  // alpha step (of the multi-shift recursion where ms is set) from the partial
+  // sums lp (rows of lprow, lcnt valid) while the others hop.  lp2 (ms only):
+  // lcnt2 partial sums of |p|^2.
   CgScalars *sc;
-  // lead > 0: the first `lead` blocks (one per system) do the alpha step from
-  // the partial sums lp (rows of lprow, lcnt valid) while the others hop.
-  int lead, lprow;
-  const double *lp;
+  MsScalars *ms;
+  int lead, lprow, lcnt2;
+  const double *lp, *lp2;
   Counts lcnt;
-  // nullable: instead of storing out, r -= alpha_sys * out for the active
-  // systems; `partial` then receives the sums of |r|^2.
+  // r (nullable): instead of storing out, r = rin - alpha (out + sigma ps),
+  // alpha that of sc for active systems (others: r = rin), or 1 where sc is
+  // NULL; `partial` then receives the sums of |r|^2.  ps is nullable, r may
+  // be rin.
   void *r;
+  const void *rin, *ps;
+  double sigma;
 };
 
 // nr: right-hand sides per block of the colour-split form (1..4; reduced to
@@ -166,46 +197,25 @@ hipError_t launch_convert(void *out, int prec_out, const void *in, int prec_in, 
 // (rows of prow); x, p, r in prec.  Also the state update of the iteration.
 hipError_t launch_cg_update_xp(void *x, void *p, const void *r, CgScalars *s, const double *rr_partial, int prow,
                                const Counts &counts, double delta, const FieldShape &f, int prec, hipStream_t st);
-// r = b - q and partial |r|^2 (FP64)
-hipError_t launch_residual(void *r, const void *b, const void *q, double *partial, const FieldShape &f,
-                           hipStream_t st);
 // With set_b2: b2 = sum(partial), stop2 = tol^2 b2, counters reset.  Otherwise
 // rho = sum(partial) for a freshly computed FP64 residual, and every system
 // that is neither converged nor broken down is (re)activated.
-hipError_t launch_cg_restart(CgScalars *s, const double *partial, int nblk, int nsys, double tol, int set_b2,
-                             hipStream_t st);
+hipError_t launch_cg_restart(CgScalars *s, const double *partial, int prow, const Counts &counts, int nsys, double tol,
+                             int set_b2, hipStream_t st);
 // x64 += x32, then x32 = 0
 hipError_t launch_accum_x(void *x64, void *x32, const FieldShape &f, hipStream_t st);
 
-// Multi-shift CG (see blas.hip for the recurrences).  One system (one rhs of
-// a single lattice); shift k's fields are `fstride` complex elements apart.
-constexpr int MAXSHIFT = 32;
-struct ShiftList {
-  double v[MAXSHIFT];
-};
-struct MsScalars {
-  double rr;          // <r, r> of the base recursion
-  double pAp;         // <p, (A + sigma0) p>
-  double alpha, alpha_old, beta, beta_old;
-  double b2, stop2;   // ||b||^2, tol^2 ||b||^2
-  double sigma0;      // base (smallest) shift
-  int iters, active, status, nshift, base, pad;
-  double delta[MAXSHIFT];   // sigma_k - sigma0
-  double zeta[MAXSHIFT], zeta_old[MAXSHIFT], zeta_new[MAXSHIFT];
-  double as[MAXSHIFT], bs[MAXSHIFT];   // shifted alpha_k, beta_k
-  int sact[MAXSHIFT];     // shift k is still updated
-  int upd[MAXSHIFT];      // shift k's x update is due in this iteration
-  int siters[MAXSHIFT];   // iterations that updated shift k
-};
 hipError_t launch_ms_init(MsScalars *s, const double *b2_partial, int nblk, const ShiftList &delta, int nshift,
                           int base, double sigma0, double tol, hipStream_t st);
-hipError_t launch_ms_alpha(MsScalars *s, const double *uu_partial, int prow, const Counts &counts,
-                           const double *pp_partial, int nblk_pp, hipStream_t st);
-hipError_t launch_ms_update_r(void *r, const void *q, const MsScalars *s, double *partial, const FieldShape &f,
-                              hipStream_t st);
-hipError_t launch_ms_beta(MsScalars *s, const double *rr_partial, int nblk, hipStream_t st);
-hipError_t launch_ms_update_xp(void *x, void *p, const void *r, const MsScalars *s, long long fstride,
-                               const FieldShape &f, int nshift, hipStream_t st);
+// Base shift of an iteration: x += alpha p, p = r + beta p, and the scalars
+// of every shift for ring slot `slot`, beta from the partial sums of |r|^2
+// (cnt of them).  pp (nullable): receives *npp partial sums of the new |p|^2.
+hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, const double *rr_partial, int cnt,
+                                 int slot, double *pp, int *npp, const FieldShape &f, hipStream_t st);
+// The updates of the other shifts for the n iterations of ring slots 0..n-1
+// (residuals `ring`, MSRING fields fstride apart).
+hipError_t launch_ms_update_xp(void *x, void *p, const void *ring, const MsScalars *s, long long fstride,
+                               const FieldShape &f, int n, hipStream_t st);
 
 // clover.hip (one lattice per call; the caller offsets the pointers).
 // Clover field: [parity][chirality block][d(2d+1)][stride] complex, the upper
