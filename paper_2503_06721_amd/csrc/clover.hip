@@ -31,6 +31,12 @@ __device__ __forceinline__ void plane_dirs(int p, int &mu, int &nu) {
 // NB x NB Hermitian block; entry (j, i) is its conjugate.
 __host__ __device__ constexpr int tri_index(int NB, int i, int j) { return i * NB - i * (i - 1) / 2 + (j - i); }
 
+// Hermitian n x n matrices as n^2 reals: the diagonal, then Re and Im of the
+// entries (i, j), i < j; position of that pair's real part.
+__host__ __device__ constexpr int herm_pair(int n, int i, int j) {
+  return n + 2 * (i * n - i * (i + 1) / 2 + (j - i - 1));
+}
+
 // Entry (i, j) of a packed Hermitian block (any i, j).
 template <typename T>
 __device__ __forceinline__ cplx<T> herm_entry(const cplx<T> *P, size_t es, int NB, int i, int j) {
@@ -51,43 +57,54 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n) {
 
 // Sites c + a e_lo + b e_hi (|a|, |b| <= 1) around one site in the plane
 // (lo, hi), lexicographic: only the two coordinates that move are wrapped,
-// by compare and select (no integer division).
+// by compare and select (no integer division).  Site indices are 32-bit (a
+// lattice has at most 2^30 sites).
 struct PlaneNb {
-  long long base, slo, shi;
-  int clo, chi, Llo, Lhi;
-  __device__ __forceinline__ static long long pick(int i, long long v0, long long v1, long long v2, long long v3) {
+  int base, slo, shi, clo, chi, Llo, Lhi;
+  __device__ __forceinline__ static int pick(int i, int v0, int v1, int v2, int v3) {
     return i == 0 ? v0 : i == 1 ? v1 : i == 2 ? v2 : v3;
   }
-  __device__ __forceinline__ PlaneNb(const Geom &g, const int (&c)[4], size_t lex, int lo, int hi) {
-    const long long sz = g.Z, sy = (long long)g.Y * g.Z, sx = sy * g.X;
-    base = (long long)lex;
+  __device__ __forceinline__ PlaneNb(const Geom &g, const int (&c)[4], unsigned lex, int lo, int hi) {
+    const int sz = g.Z, sy = g.Y * g.Z, sx = sy * g.X;
+    base = (int)lex;
     slo = pick(lo, sx, sy, sz, 1);
     shi = pick(hi, sx, sy, sz, 1);
-    clo = (int)pick(lo, c[0], c[1], c[2], c[3]);
-    chi = (int)pick(hi, c[0], c[1], c[2], c[3]);
-    Llo = (int)pick(lo, g.T, g.X, g.Y, g.Z);
-    Lhi = (int)pick(hi, g.T, g.X, g.Y, g.Z);
+    clo = pick(lo, c[0], c[1], c[2], c[3]);
+    chi = pick(hi, c[0], c[1], c[2], c[3]);
+    Llo = pick(lo, g.T, g.X, g.Y, g.Z);
+    Lhi = pick(hi, g.T, g.X, g.Y, g.Z);
   }
-  __device__ __forceinline__ size_t at(int a, int b) const {
+  __device__ __forceinline__ unsigned at(int a, int b) const {
     const int qa = clo + a, qb = chi + b;
     const int da = qa < 0 ? a + Llo : qa >= Llo ? a - Llo : a;
     const int db = qb < 0 ? b + Lhi : qb >= Lhi ? b - Lhi : b;
-    return (size_t)(base + da * slo + db * shi);
+    return (unsigned)(base + da * slo + db * shi);
   }
 };
+// Coordinates of lexicographic site lex.
+__device__ __forceinline__ void lex_coords(const Geom &g, unsigned lex, int (&c)[4]) {
+  unsigned r = lex;
+  c[3] = (int)(r % (unsigned)g.Z); r /= (unsigned)g.Z;
+  c[2] = (int)(r % (unsigned)g.Y); r /= (unsigned)g.Y;
+  c[1] = (int)(r % (unsigned)g.X);
+  c[0] = (int)(r / (unsigned)g.X);
+}
 
 // The clover kernels read the fundamental links from a structure-of-arrays
 // copy Us[mu][N*N][V] (lexicographic site minor; k_links_soa), so that the
-// lanes of a wavefront, on consecutive sites, read consecutive addresses.
+// lanes of a wavefront, on consecutive sites, read consecutive addresses.  The
+// direction (and plane) is the same for all lanes of a wavefront, so each
+// entry row has a scalar base address and a lane one 32-bit offset (16 bytes a
+// site, below 4 GiB for any lattice whose scratch fits the card).
 template <int N>
-__device__ __forceinline__ void load_link(cplx<double> (&u)[N][N], const cplx<double> *Us, size_t V, size_t lex,
+__device__ __forceinline__ void load_link(cplx<double> (&u)[N][N], const cplx<double> *Us, size_t V, unsigned lex,
                                           int mu, bool dag) {
-  const cplx<double> *p = Us + (size_t)mu * N * N * V + lex;
+  const cplx<double> *p = Us + (size_t)__builtin_amdgcn_readfirstlane(mu) * N * N * V;
 #pragma unroll
   for (int i = 0; i < N; ++i)
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      const cplx<double> v = p[(size_t)(dag ? j * N + i : i * N + j) * V];
+      const cplx<double> v = *at(p + (size_t)(dag ? j * N + i : i * N + j) * V, lex);
       u[i][j] = dag ? mk(v.re, -v.im) : v;
     }
 }
@@ -165,24 +182,20 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
                                                   Geom g) {
   constexpr int D = rep_dim(N, REP);
   const size_t V = 2 * (size_t)g.Vh;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned gid = blockIdx.x * 256u + threadIdx.x;
   // 64-site chunks, the six planes of a chunk in consecutive wavefronts (the
   // planes that share a link direction read it close together in time)
-  const size_t chunk = gid / 384;
-  const int r6 = (int)(gid - chunk * 384);
-  const int p = r6 >> 6;
-  const size_t lex = chunk * 64 + (r6 & 63);
+  const unsigned chunk = gid / 384u;
+  const int r6 = (int)(gid - chunk * 384u);
+  const int p = __builtin_amdgcn_readfirstlane(r6 >> 6);
+  const unsigned lex = chunk * 64u + (r6 & 63);
   if (lex >= V) return;
   int mu, nu;
   plane_dirs(p, mu, nu);
-  size_t r = lex;
   int c[4];
-  c[3] = (int)(r % g.Z); r /= g.Z;
-  c[2] = (int)(r % g.Y); r /= g.Y;
-  c[1] = (int)(r % g.X);
-  c[0] = (int)(r / g.X);
+  lex_coords(g, lex, c);
   const PlaneNb pn(g, c, lex, mu, nu);
-  cplx<double> *Fp = F + (size_t)p * D * D * V + lex;
+  cplx<double> *Fp = F + (size_t)p * D * D * V;
   if constexpr (REP == 0) {
     // fundamental representation (R = 1): the four leaves summed in
     // registers, F = (Q - Q^+)/8 written once (the other representations
@@ -233,7 +246,7 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
       for (int B = 0; B < DA; ++B) {
         const cplx<double> v = FUND ? mk(0.125 * (acc[A][B].re - acc[B][A].re), 0.125 * (acc[A][B].im + acc[B][A].im))
                                     : 0.125 * acc[A][B];
-        Fp[(size_t)(A * D + B) * V] = v;
+        *at(Fp + (size_t)(A * D + B) * V, lex) = v;
       }
     return;
   }
@@ -259,9 +272,9 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
       for (int B = 0; B < D; ++B) {
         const cplx<double> rab = rep_entry<N, REP>(L, A, B), rba = rep_entry<N, REP>(L, B, A);
         cplx<double> v = mk(0.125 * (rab.re - rba.re), 0.125 * (rab.im + rba.im));
-        const size_t o = (size_t)(A * D + B) * V;
-        if (k > 0) v = v + Fp[o];
-        Fp[o] = v;
+        cplx<double> *o = at(Fp + (size_t)(A * D + B) * V, lex);
+        if (k > 0) v = v + *o;
+        *o = v;
       }
   }
 }
@@ -272,149 +285,350 @@ struct SigmaBlocks {
   cplx<double> v[6][2][2][2];
 };
 
-// Gauss-Jordan inverse with partial pivoting of the n x n matrix a (destroyed).
+// Hermitian NB x NB matrices in registers: the real diagonal and the upper
+// triangle, every index a compile-time constant.
 template <int NB>
-__device__ void invert(cplx<double> (&a)[NB][NB], cplx<double> (&inv)[NB][NB]) {
-  for (int i = 0; i < NB; ++i)
-    for (int j = 0; j < NB; ++j) inv[i][j] = mk(i == j ? 1.0 : 0.0, 0.0);
-  for (int col = 0; col < NB; ++col) {
-    int piv = col;
-    double best = a[col][col].re * a[col][col].re + a[col][col].im * a[col][col].im;
-    for (int r = col + 1; r < NB; ++r) {
-      const double m2 = a[r][col].re * a[r][col].re + a[r][col].im * a[r][col].im;
-      if (m2 > best) {
-        best = m2;
-        piv = r;
-      }
+struct Herm {
+  double d[NB];
+  cplx<double> o[NB * (NB - 1) / 2];
+  static constexpr int at(int i, int j) { return i * (NB - 1) - i * (i - 1) / 2 + (j - i - 1); }   // i < j
+  // entry (i, j), i != j
+  __device__ __forceinline__ cplx<double> off(int i, int j) const {
+    if (i < j) return o[at(i, j)];
+    const cplx<double> v = o[at(j, i)];
+    return mk(v.re, -v.im);
+  }
+};
+
+// f a b + g for commuting a, b (the product is then Hermitian: only its
+// diagonal and upper triangle are formed), g times the unit matrix.
+template <int NB>
+__device__ __forceinline__ Herm<NB> herm_mul(const Herm<NB> &a, const Herm<NB> &b, double f, double g) {
+  Herm<NB> r;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    double s = a.d[i] * b.d[i];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      if (k == i) continue;
+      const cplx<double> x = a.off(i, k), y = b.off(i, k);   // b_ki = conj(b_ik)
+      s = fma(x.re, y.re, s);
+      s = fma(x.im, y.im, s);
     }
-    if (piv != col)
-      for (int j = 0; j < NB; ++j) {
-        const cplx<double> t1 = a[col][j], t2 = inv[col][j];
-        a[col][j] = a[piv][j];
-        inv[col][j] = inv[piv][j];
-        a[piv][j] = t1;
-        inv[piv][j] = t2;
-      }
-    const cplx<double> d = a[col][col];
-    const double dn = 1.0 / (d.re * d.re + d.im * d.im);
-    const cplx<double> di = mk(d.re * dn, -d.im * dn);
-    for (int j = 0; j < NB; ++j) {
-      a[col][j] = cmul(a[col][j], di);
-      inv[col][j] = cmul(inv[col][j], di);
-    }
-    for (int r = 0; r < NB; ++r) {
-      if (r == col) continue;
-      const cplx<double> f = a[r][col];
-      for (int j = 0; j < NB; ++j) {
-        a[r][j] = a[r][j] - cmul(f, a[col][j]);
-        inv[r][j] = inv[r][j] - cmul(f, inv[col][j]);
-      }
+    r.d[i] = fma(f, s, g);
+#pragma unroll
+    for (int j = i + 1; j < NB; ++j) {
+      const cplx<double> aij = a.off(i, j), bij = b.off(i, j);
+      cplx<double> t = mk(a.d[i] * bij.re, a.d[i] * bij.im);
+      t.re = fma(b.d[j], aij.re, t.re);
+      t.im = fma(b.d[j], aij.im, t.im);
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (k != i && k != j) t = cfma(a.off(i, k), b.off(k, j), t);
+      r.o[Herm<NB>::at(i, j)] = mk(f * t.re, f * t.im);
     }
   }
+  return r;
 }
 
-// e = exp(a) by scaling and squaring of the Taylor series (a destroyed).
-template <int NB>
-__device__ void expm(cplx<double> (&a)[NB][NB], cplx<double> (&e)[NB][NB]) {
-  double nrm = 0.0;   // max column sum
-  for (int j = 0; j < NB; ++j) {
-    double s = 0.0;
-    for (int i = 0; i < NB; ++i) s += sqrt(a[i][j].re * a[i][j].re + a[i][j].im * a[i][j].im);
-    nrm = s > nrm ? s : nrm;
-  }
+// Scaling 2^-sq that brings the norm nrm below 1/4, where the Taylor series of
+// degree kTaylor gives exp: the first dropped term is below 0.25^13 / 13! ~ 2e-18.
+constexpr int kTaylor = 12;
+__device__ __forceinline__ int exp_squarings(double nrm) {
   int sq = 0;
   while (nrm > 0.25 && sq < 60) {
     nrm *= 0.5;
     ++sq;
   }
-  const double sc = ldexp(1.0, -sq);
-  for (int i = 0; i < NB; ++i)
-    for (int j = 0; j < NB; ++j) a[i][j] = sc * a[i][j];
-  // Horner: e = I + a (I + a/2 (I + a/3 (... (I + a/K))))
-  // (||a|| <= 1/4: the first dropped term is below 0.25^13 / 13! ~ 2e-18)
-  constexpr int K = 12;
-  cplx<double> t[NB][NB];
-  for (int i = 0; i < NB; ++i)
-    for (int j = 0; j < NB; ++j) e[i][j] = mk(i == j ? 1.0 : 0.0, 0.0);
-  for (int k = K; k >= 1; --k) {
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) {
-        cplx<double> s = mk(0.0, 0.0);
-        for (int l = 0; l < NB; ++l) s = cfma(a[i][l], e[l][j], s);
-        t[i][j] = (1.0 / k) * s;
-      }
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) e[i][j] = t[i][j] + mk(i == j ? 1.0 : 0.0, 0.0);
-  }
-  for (int q = 0; q < sq; ++q) {
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) {
-        cplx<double> s = mk(0.0, 0.0);
-        for (int l = 0; l < NB; ++l) s = cfma(e[i][l], e[l][j], s);
-        t[i][j] = s;
-      }
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) e[i][j] = t[i][j];
-  }
+  return sq;
 }
 
-// Thread per (site, chirality block c): assemble the block from F, add the
-// mass term (or exponentiate), invert on odd sites, store in precision T.
-// Clover field layout: [parity][c][row][col][stride] complex.
+// Exponential form, d_R <= 3: thread per (site, chirality block), the block
+// index fastest as in k_clover_finish_reg.  Everything is a polynomial in the
+// Hermitian A = C / (4 + m) (odd sites: -A), so a product costs its upper
+// triangle (432 FMA for d_R = 3 instead of 864) and three matrices stay in
+// registers (two waves per SIMD): bound by FP64 arithmetic.  SU(3) FUND 32^4:
+// 3604 us with general matrices, which spilled to scratch; 575 us.
 template <int D, typename T>
-__global__ __launch_bounds__(64) void k_clover_finish(const cplx<double> *__restrict__ F, void *__restrict__ clov,
-                                                      Geom g, SigmaBlocks S, double m0, double csw, int expo) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_clover_finish_exp(
+    const cplx<double> *__restrict__ F, void *__restrict__ clov, Geom g, SigmaBlocks S, double m0, double csw) {
   constexpr int NB = 2 * D;
   const size_t V = 2 * (size_t)g.Vh;
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= 2 * V) return;
-  const int c = (int)(gid / V);
-  const size_t lex = gid - (size_t)c * V;
-  size_t r = lex;
+  const int c = (int)(gid & 1);
+  const unsigned lex = (unsigned)(gid >> 1);
+  unsigned r = lex;
   const int z = (int)(r % g.Z); r /= g.Z;
   const int y = (int)(r % g.Y); r /= g.Y;
   const int x = (int)(r % g.X);
   const int t = (int)(r / g.X);
   const int par = (t + x + y + z) & 1;
   const size_t cb = lex >> 1;
-  cplx<double> M[NB][NB];
-  // (i/4) c_sw sum_p S[p][c][s][t] F_p[a][b]
-  for (int s = 0; s < 2; ++s)
-    for (int a = 0; a < D; ++a)
-      for (int tt = 0; tt < 2; ++tt)
-        for (int b = 0; b < D; ++b) {
-          cplx<double> acc = mk(0.0, 0.0);
-          for (int p = 0; p < 6; ++p) acc = cfma(S.v[p][c][s][tt], F[((size_t)p * D * D + a * D + b) * V + lex], acc);
-          M[s * D + a][tt * D + b] = mk(-0.25 * csw * acc.im, 0.25 * csw * acc.re);   // (i/4) c_sw acc
-        }
-  cplx<double> out[NB][NB];
   const double m4 = 4.0 + m0;
-  if (!expo) {
-    for (int i = 0; i < NB; ++i) M[i][i].re += m4;
-    if (par == 0) {
-      for (int i = 0; i < NB; ++i)
-        for (int j = 0; j < NB; ++j) out[i][j] = M[i][j];
-    } else {
-      invert<NB>(M, out);
-    }
-  } else {
-    // even: (4+m) exp(M/(4+m)); odd: exp(-M/(4+m))/(4+m)
-    const double f = (par == 0 ? 1.0 : -1.0) / m4;
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) M[i][j] = f * M[i][j];
-    expm<NB>(M, out);
-    const double sc = par == 0 ? m4 : 1.0 / m4;
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) out[i][j] = sc * out[i][j];
+  // A = f sum_p (i S_p) F_p, f = c_sw / (4 (4 + m)); i S_p and F_p are
+  // anti-Hermitian and Hermitian-times-i, their products' sum Hermitian
+  const double f = (par == 0 ? 0.25 : -0.25) * csw / m4;
+  Herm<NB> A;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) A.d[i] = 0.0;
+#pragma unroll
+  for (int k = 0; k < NB * (NB - 1) / 2; ++k) A.o[k] = mk(0.0, 0.0);
+#pragma unroll
+  for (int p = 0; p < 6; ++p) {
+    cplx<double> fp[D][D];
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+      for (int b = 0; b < D; ++b) fp[a][b] = F[((size_t)p * D * D + a * D + b) * V + lex];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int tt = s2; tt < 2; ++tt) {
+        const cplx<double> sv = S.v[p][c][s2][tt];
+#pragma unroll
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+          for (int b = 0; b < D; ++b) {
+            const int i = s2 * D + a, j = tt * D + b;
+            if (i == j) {   // Re(i sv fp) = -Im(sv fp)
+              A.d[i] = fma(-sv.re, fp[a][b].im, A.d[i]);
+              A.d[i] = fma(-sv.im, fp[a][b].re, A.d[i]);
+            } else if (i < j) {
+              cplx<double> &o = A.o[Herm<NB>::at(i, j)];
+              o = cfma(mk(-sv.im, sv.re), fp[a][b], o);
+            }
+          }
+      }
+    // one plane's F entries live at a time
+    __builtin_amdgcn_sched_barrier(0);
   }
+  // largest column sum of |A| (Hermitian: row sums)
+  double nrm = 0.0;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j == i) s += fabs(A.d[i]);
+      else {
+        const cplx<double> v = A.off(i, j);
+        s += sqrt(v.re * v.re + v.im * v.im);
+      }
+    }
+    nrm = s > nrm ? s : nrm;
+  }
+  const int sq = exp_squarings(nrm * fabs(f));
+  const double sc = ldexp(f, -sq);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) A.d[i] *= sc;
+#pragma unroll
+  for (int k = 0; k < NB * (NB - 1) / 2; ++k) A.o[k] = sc * A.o[k];
+  // Horner: E = 1 + A (1 + A/2 (1 + A/3 (... (1 + A/K)))), then the squarings
+  Herm<NB> E;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) E.d[i] = fma(1.0 / kTaylor, A.d[i], 1.0);
+#pragma unroll
+  for (int k = 0; k < NB * (NB - 1) / 2; ++k) E.o[k] = (1.0 / kTaylor) * A.o[k];
+#pragma unroll 1
+  for (int k = kTaylor - 1; k >= 1; --k) E = herm_mul<NB>(A, E, 1.0 / k, 1.0);
+#pragma unroll 1
+  for (int q = 0; q < sq; ++q) E = herm_mul<NB>(E, E, 1.0, 0.0);
+  // even: (4+m) exp(A); odd: exp(-A)/(4+m)
+  const double e = par == 0 ? m4 : 1.0 / m4;
   constexpr int NT = NB * (NB + 1) / 2;
   cplx<T> *dst = static_cast<cplx<T> *>(clov) + ((size_t)(par * 2 + c) * NT) * g.stride + cb;
-  for (int i = 0; i < NB; ++i)
-    for (int j = i; j < NB; ++j) {
-      // the computed block is Hermitian up to rounding: store the mean of (i,j) and conj(j,i)
-      const double re = 0.5 * (out[i][j].re + out[j][i].re), im = 0.5 * (out[i][j].im - out[j][i].im);
-      dst[(size_t)tri_index(NB, i, j) * g.stride] = mk<T>((T)re, (T)(i == j ? 0.0 : im));
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    dst[(size_t)tri_index(NB, i, i) * g.stride] = mk<T>((T)(e * E.d[i]), (T)0);
+#pragma unroll
+    for (int j = i + 1; j < NB; ++j) {
+      const cplx<double> v = E.off(i, j);
+      dst[(size_t)tri_index(NB, i, j) * g.stride] = mk<T>((T)(e * v.re), (T)(e * v.im));
     }
+  }
+}
+
+// Exchange-method (Gauss-Jordan) inverse with partial pivoting of one NB x NB
+// matrix by NB lanes, lane i holding row i in w; every lane of the 64-lane
+// block calls it (barriers).  Step k takes the row p_k of largest |w_k| not
+// yet taken; afterwards lane p_k, whose `mine` is k, holds w[j] =
+// (A^-1)[k][p_j].  The columns rotate one place per step, so that the step's
+// column is always 0 and w stays in registers.  Returns log|det A|.
+template <int NB>
+__device__ __forceinline__ double rows_exchange(cplx<double> (&w)[NB], cplx<double> (*sh)[NB + 1], int *perm, int i,
+                                                bool lane_used, int &mine) {
+  bool taken = false;
+  double ld = 0.0;
+  mine = 0;
+#pragma unroll 1
+  for (int k = 0; k < NB; ++k) {
+    __syncthreads();
+    if (lane_used) sh[i][NB] = mk(taken ? -1.0 : w[0].re * w[0].re + w[0].im * w[0].im, 0.0);
+    __syncthreads();
+    int p = 0;
+    double best = -1.0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const double v = sh[q][NB].re;
+      p = v > best ? q : p;
+      best = v > best ? v : best;
+    }
+    ld += 0.5 * log(best);
+    if (i == p) {
+      const cplx<double> d = w[0];
+      const double dn = 1.0 / (d.re * d.re + d.im * d.im);
+      const cplx<double> di = mk(d.re * dn, -d.im * dn);
+      w[0] = mk(1.0, 0.0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) w[j] = cmul(w[j], di);
+      if (lane_used) {
+        perm[k] = p;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) sh[0][j] = w[j];
+      }
+      taken = true;
+      mine = k;
+    }
+    __syncthreads();
+    if (i != p) {
+      const cplx<double> f = w[0];
+      w[0] = mk(0.0, 0.0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) w[j] = w[j] - cmul(f, sh[0][j]);
+    }
+    const cplx<double> w0 = w[0];
+#pragma unroll
+    for (int j = 0; j + 1 < NB; ++j) w[j] = w[j + 1];
+    w[NB - 1] = w0;
+  }
+  __syncthreads();
+  return ld;
+}
+
+// Larger blocks (d_R = 6, and d_R = 4 in the exponential form): NB = 2 d_R
+// lanes per (site, chirality block), lane i holding row i and reading other
+// rows from LDS; 64-lane blocks of MPB matrices, the lanes past them following
+// the barriers.  Exponential form: Horner and squarings as above on general
+// rows.  Regular form: D_ee as assembled on even sites, on odd sites its
+// inverse (rows_exchange).  (One lane per whole matrix spills it to scratch: SU(3) SYM
+// 16^4, the whole field: 5025 us so, 1160 us here, regular; 11244 and 2571 us
+// exponential.)
+template <int D, typename T>
+__global__ __launch_bounds__(64) void k_clover_finish_rows(const cplx<double> *__restrict__ F, void *__restrict__ clov,
+                                                           Geom g, SigmaBlocks S, double m0, double csw, int expo) {
+  constexpr int NB = 2 * D, MPB = 64 / NB;
+  __shared__ cplx<double> sh[MPB][NB][NB + 1];
+  const size_t V = 2 * (size_t)g.Vh;
+  const int mloc0 = (int)threadIdx.x / NB;
+  const bool lane_used = mloc0 < MPB;
+  const int mloc = lane_used ? mloc0 : MPB - 1;
+  const int i = lane_used ? (int)threadIdx.x - mloc * NB : 0;   // row of this lane
+  const size_t m0g = (size_t)blockIdx.x * MPB + mloc;
+  const bool valid = lane_used && m0g < 2 * V;
+  const size_t mg = m0g < 2 * V ? m0g : 2 * V - 1;
+  const int c = (int)(mg / V);
+  const unsigned lex = (unsigned)(mg - (size_t)c * V);
+  unsigned r = lex;
+  const int z = (int)(r % g.Z); r /= g.Z;
+  const int y = (int)(r % g.Y); r /= g.Y;
+  const int x = (int)(r % g.X);
+  const int t = (int)(r / g.X);
+  const int par = (t + x + y + z) & 1;
+  const size_t cb = lex >> 1;
+  const int si = i / D, ai = i - si * D;   // row i = (spin si, colour ai)
+  const double m4 = 4.0 + m0;
+  // row i of (i/4) c_sw sum_p S[p][c][s][t] F_p[a][b]
+  cplx<double> a[NB];
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+    for (int b = 0; b < D; ++b) {
+      cplx<double> acc = mk(0.0, 0.0);
+#pragma unroll
+      for (int p = 0; p < 6; ++p)
+        acc = cfma(S.v[p][c][si][tt], F[((size_t)p * D * D + ai * D + b) * V + lex], acc);
+      a[tt * D + b] = mk(-0.25 * csw * acc.im, 0.25 * csw * acc.re);
+    }
+  double scale = 1.0;
+  if (expo) {   // even: (4+m) exp(a/(4+m)); odd: exp(-a/(4+m))/(4+m)
+    double rs = 0.0;   // row sum of |a|: the largest is the norm (Hermitian)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) rs += sqrt(a[j].re * a[j].re + a[j].im * a[j].im);
+    if (lane_used) sh[mloc][i][NB] = mk(rs, 0.0);
+    __syncthreads();
+    double nrm = 0.0;
+    for (int j = 0; j < NB; ++j) nrm = sh[mloc][j][NB].re > nrm ? sh[mloc][j][NB].re : nrm;
+    const double f = (par == 0 ? 1.0 : -1.0) / m4;
+    const int sq = exp_squarings(nrm * fabs(f));
+    int sqmax = sq;   // every lane takes part in every barrier
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const int o = __shfl_xor(sqmax, off, 64);
+      sqmax = o > sqmax ? o : sqmax;
+    }
+    const double sc = ldexp(f, -sq);
+    cplx<double> e[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      a[j] = sc * a[j];
+      e[j] = mk(i == j ? 1.0 : 0.0, 0.0);
+    }
+    for (int k = kTaylor; k >= -sqmax + 1; --k) {   // k >= 1: Horner; k <= 0: squarings
+      __syncthreads();
+      if (lane_used)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) sh[mloc][i][j] = e[j];
+      __syncthreads();
+      const bool horner = k >= 1, on = horner || 1 - k <= sq;
+      const double rk = horner ? 1.0 / k : 1.0;
+      cplx<double> row[NB], n[NB];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) row[q] = mk(horner ? a[q].re : e[q].re, horner ? a[q].im : e[q].im);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        cplx<double> s = mk(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) s = cfma(row[q], sh[mloc][q][j], s);
+        n[j] = mk(fma(rk, s.re, horner && i == j ? 1.0 : 0.0), rk * s.im);
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) e[j] = mk(on ? n[j].re : e[j].re, on ? n[j].im : e[j].im);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) a[j] = e[j];
+    scale = par == 0 ? m4 : 1.0 / m4;
+    __syncthreads();
+    if (lane_used)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) sh[mloc][i][j] = a[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) a[j].re += i == j ? m4 : 0.0;
+    // every matrix goes through the steps (barriers); even sites store a as it is
+    cplx<double> w[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) w[j] = a[j];
+    __shared__ int perm[MPB][NB];
+    int mine;
+    rows_exchange<NB>(w, sh[mloc], perm[mloc], i, lane_used, mine);
+    if (lane_used)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        if (par == 0) sh[mloc][i][j] = a[j];
+        else sh[mloc][mine][perm[mloc][j]] = w[j];
+      }
+  }
+  __syncthreads();
+  if (!valid) return;
+  constexpr int NT = NB * (NB + 1) / 2;
+  cplx<T> *dst = static_cast<cplx<T> *>(clov) + ((size_t)(par * 2 + c) * NT) * g.stride + cb;
+  for (int j = i; j < NB; ++j) {
+    // Hermitian up to rounding: store the mean of (i,j) and conj(j,i)
+    const cplx<double> u = sh[mloc][i][j], l = sh[mloc][j][i];
+    const double re = scale * 0.5 * (u.re + l.re), im = scale * 0.5 * (u.im - l.im);
+    dst[(size_t)tri_index(NB, i, j) * g.stride] = mk<T>((T)re, (T)(i == j ? 0.0 : im));
+  }
 }
 
 // In-place Gauss-Jordan inverse with partial pivoting of the NB x NB matrix
@@ -476,8 +690,9 @@ __device__ __forceinline__ void invert_in_place(cplx<double> (&a)[NB][NB]) {
   }
 }
 
-// Regular clover (no exponential), d_R <= 4: as k_clover_finish with the
-// block in registers throughout.  Thread per (site, chirality block), the
+// Regular clover (no exponential), d_R <= 4: assemble the block from F, add
+// the mass term, invert on odd sites, store in precision T, with the block in
+// registers throughout.  Thread per (site, chirality block), the
 // block index fastest, so that the two threads of a site read the same F
 // entries together (F comes from HBM once).
 template <int D, typename T>
@@ -588,29 +803,38 @@ static hipError_t F_launch(const void *U, double *F, const Geom &g, hipStream_t 
   return hipGetLastError();
 }
 
-template <int D>
-static hipError_t finish_launch(const double *F, void *clov, const Geom &g, const SigmaBlocks &S, double m0,
-                                double csw, int expo, int prec, hipStream_t st) {
+template <int D, typename T>
+static hipError_t finish_launch_t(const double *F, void *clov, const Geom &g, const SigmaBlocks &S, double m0,
+                                  double csw, int expo, hipStream_t st) {
   const size_t n = 2 * 2 * (size_t)g.Vh;
-  const dim3 grid((unsigned)((n + 63) / 64));
-  if constexpr (D <= 4) {
-    if (!expo) {
-      if (prec == 0)
-        hipLaunchKernelGGL((k_clover_finish_reg<D, double>), grid, dim3(64), 0, st, (const cplx<double> *)F, clov, g,
-                           S, m0, csw);
-      else
-        hipLaunchKernelGGL((k_clover_finish_reg<D, float>), grid, dim3(64), 0, st, (const cplx<double> *)F, clov, g,
-                           S, m0, csw);
+  const cplx<double> *f = (const cplx<double> *)F;
+  if constexpr (D <= 3) {
+    if (expo) {
+      hipLaunchKernelGGL((k_clover_finish_exp<D, T>), dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, f, clov, g, S,
+                         m0, csw);
       return hipGetLastError();
     }
   }
-  if (prec == 0)
-    hipLaunchKernelGGL((k_clover_finish<D, double>), grid, dim3(64), 0, st, (const cplx<double> *)F, clov, g, S, m0,
-                       csw, expo);
-  else
-    hipLaunchKernelGGL((k_clover_finish<D, float>), grid, dim3(64), 0, st, (const cplx<double> *)F, clov, g, S, m0,
-                       csw, expo);
+  if constexpr (D <= 4) {
+    if (!expo) {
+      hipLaunchKernelGGL((k_clover_finish_reg<D, T>), dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, f, clov, g, S,
+                         m0, csw);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (D > 3) {
+    constexpr int MPB = 64 / (2 * D);
+    hipLaunchKernelGGL((k_clover_finish_rows<D, T>), dim3((unsigned)((n + MPB - 1) / MPB)), dim3(64), 0, st, f, clov, g,
+                       S, m0, csw, expo);
+  }
   return hipGetLastError();
+}
+
+template <int D>
+static hipError_t finish_launch(const double *F, void *clov, const Geom &g, const SigmaBlocks &S, double m0,
+                                double csw, int expo, int prec, hipStream_t st) {
+  return prec == 0 ? finish_launch_t<D, double>(F, clov, g, S, m0, csw, expo, st)
+                   : finish_launch_t<D, float>(F, clov, g, S, m0, csw, expo, st);
 }
 
 static SigmaBlocks sigma_blocks() {
@@ -724,70 +948,111 @@ bool clover_supported(int d) { return d == 2 || d == 3 || d == 4 || d == 6; }
 // link's force receives +-B^+ g B with B the fundamental path from the
 // leaf's corner up to (forward) or through (dagger) the link.
 //
-// Pipeline (one lattice): insertion K per (site, chirality) -> leaf matrices
-// g per (plane, site) -> gather over the 24 (leaf, corner) pairs holding each
-// link.  Scratch: K [2][6][d][d][V], g [6][4][N][N][V] complex FP64.
+// Pipeline (one lattice): insertion K per site -> leaf matrices g per (plane,
+// site) -> gather over the 24 (leaf, corner) pairs holding each link; in the
+// fundamental representation the gather takes K itself (k_clover_gather_fund).
+// Scratch: K [6][d^2][V] reals, g [6][4][N^2][V] reals (Hermitian matrices: the
+// diagonal, then Re and Im of the upper triangle).
+//
+// K only needs the Hermitian B = Omega + Omega^+ (exponential form: L(A, .) maps
+// Hermitian to Hermitian): with the Hermitian sigma_p,
+//   (K_p)_ba = sum_c sum_st (sigma_p)_st (B_c)_(t b),(s a).
 
-// Thread per (site, chirality block c): Omega_c = X_c Y_c^+ (Xe non-null)
-// + cdet D_oo^{-1} (odd sites), then this block's share of Lam_p for the six
-// planes into K[c][p][b][a][V] (regular clover; the exponential form is
-// k_clover_insert_rows).
-template <int D>
-__global__ __launch_bounds__(64) void k_clover_insert(const cplx<double> *Xe, const cplx<double> *Xo,
-                                                      const cplx<double> *Ye, const cplx<double> *Yo,
-                                                      const cplx<double> *__restrict__ clov,
-                                                      const cplx<double> *__restrict__ F, cplx<double> *__restrict__ K,
-                                                      Geom g, SigmaBlocks S, double m0, double csw, double cdet) {
+// Thread per site (regular clover; the exponential form is
+// k_clover_insert_rows): B = X Y^+ + Y X^+ per chirality block, or (DET)
+// 2 cdet D_oo^{-1} on the odd sites and 0 on the even ones.  For each entry
+// (b, a), b <= a, the eight entries of B it needs are formed once and summed
+// for the six planes.  Bound by memory: SU(3) FUND 24^4 160 us writing both
+// chiralities' general matrices, 64 us (DET: 57).
+template <int D, bool DET>
+__global__ __launch_bounds__(64) void k_clover_insert(const cplx<double> *__restrict__ Xe,
+                                                      const cplx<double> *__restrict__ Xo,
+                                                      const cplx<double> *__restrict__ Ye,
+                                                      const cplx<double> *__restrict__ Yo,
+                                                      const cplx<double> *__restrict__ clov, double *__restrict__ K,
+                                                      Geom g, SigmaBlocks S, double cdet) {
   constexpr int NB = 2 * D;
+  constexpr bool HOLD = !DET && D <= 3;   // the spinors stay in registers
   const size_t V = 2 * (size_t)g.Vh;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= 2 * V) return;
-  const int c = (int)(gid / V);
-  const size_t lex = gid - (size_t)c * V;
-  size_t r = lex;
+  const unsigned lex = blockIdx.x * 64u + threadIdx.x;
+  if (lex >= V) return;
+  unsigned r = lex;
   const int z = (int)(r % g.Z); r /= g.Z;
   const int y = (int)(r % g.Y); r /= g.Y;
   const int x = (int)(r % g.X);
   const int t = (int)(r / g.X);
   const int par = (t + x + y + z) & 1;
   const size_t cb = lex >> 1;
-  cplx<double> Om[NB][NB];
-  for (int i = 0; i < NB; ++i)
-    for (int j = 0; j < NB; ++j) Om[i][j] = mk(0.0, 0.0);
-  if (Xe) {
-    const cplx<double> *X = par ? Xo : Xe, *Y = par ? Yo : Ye;
-    cplx<double> xv[NB], yv[NB];
-    for (int sl = 0; sl < 2; ++sl)
-      for (int a = 0; a < D; ++a) {
-        const size_t o = (size_t)((2 * c + sl) * D + a) * g.stride + cb;
-        xv[sl * D + a] = X[o];
-        yv[sl * D + a] = Y[o];
-      }
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j)
-        Om[i][j] = mk(xv[i].re * yv[j].re + xv[i].im * yv[j].im, xv[i].im * yv[j].re - xv[i].re * yv[j].im);
+  const cplx<double> *X = par ? Xo : Xe, *Y = par ? Yo : Ye;
+  const cplx<double> *Mi = clov + (size_t)2 * (NB * (NB + 1) / 2) * g.stride + cb;   // odd sites
+  cplx<double> xv[HOLD ? 2 * NB : 1], yv[HOLD ? 2 * NB : 1];
+  if constexpr (HOLD) {
+#pragma unroll
+    for (int k = 0; k < 2 * NB; ++k) {
+      xv[k] = X[(size_t)k * g.stride + cb];
+      yv[k] = Y[(size_t)k * g.stride + cb];
+    }
   }
-  if (cdet != 0.0 && par == 1) {
-    const cplx<double> *Mi = clov + (size_t)(2 + c) * (NB * (NB + 1) / 2) * g.stride + cb;
-    for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) Om[i][j] = Om[i][j] + cdet * herm_entry(Mi, g.stride, NB, i, j);
-  }
-  // S.v holds 2 sigma
-  for (int p = 0; p < 6; ++p)
-    for (int b = 0; b < D; ++b)
-      for (int a = 0; a < D; ++a) {
-        cplx<double> acc = mk(0.0, 0.0);
+  const auto entry = [&](int b, int a) {
+    cplx<double> bm[2][2][2];   // [c][s][t]: (B_c)_(t b),(s a)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+          if constexpr (DET) {
+            const cplx<double> m =
+                par ? herm_entry(Mi + (size_t)c * (NB * (NB + 1) / 2) * g.stride, g.stride, NB, tt * D + b, s * D + a)
+                    : mk(0.0, 0.0);
+            bm[c][s][tt] = (2.0 * cdet) * m;
+          } else {
+            const int i = (2 * c + tt) * D + b, j = (2 * c + s) * D + a;
+            cplx<double> xi, yi, xj, yj;
+            if constexpr (HOLD) {
+              xi = xv[i]; yi = yv[i]; xj = xv[j]; yj = yv[j];
+            } else {
+              xi = X[(size_t)i * g.stride + cb]; yi = Y[(size_t)i * g.stride + cb];
+              xj = X[(size_t)j * g.stride + cb]; yj = Y[(size_t)j * g.stride + cb];
+            }
+            // x_i conj(y_j) + y_i conj(x_j)
+            bm[c][s][tt] = cfma_conj(xj, yi, cfma_conj(yj, xi, mk(0.0, 0.0)));
+          }
+        }
+    for (int p = 0; p < 6; ++p) {
+      cplx<double> acc = mk(0.0, 0.0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
         for (int s = 0; s < 2; ++s)
-          for (int tt = 0; tt < 2; ++tt) acc = cfma(S.v[p][c][s][tt], Om[tt * D + b][s * D + a], acc);
-        K[(((size_t)(c * 6 + p) * D + b) * D + a) * V + lex] = 0.5 * acc;
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) acc = cfma(S.v[p][c][s][tt], bm[c][s][tt], acc);   // S.v holds 2 sigma
+      double *k = K + (size_t)p * D * D * V + lex;
+      if (b == a) {
+        k[(size_t)b * V] = 0.5 * acc.re;
+      } else {
+        const int e = herm_pair(D, b, a);
+        k[(size_t)e * V] = 0.5 * acc.re;
+        k[(size_t)(e + 1) * V] = 0.5 * acc.im;
       }
+    }
+  };
+  if constexpr (HOLD) {
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+      for (int a = b; a < D; ++a) entry(b, a);
+  } else {
+    for (int b = 0; b < D; ++b)
+      for (int a = b; a < D; ++a) entry(b, a);
+  }
 }
 
-// Exponential form: as k_clover_insert with Omega_c <- L(A_c, Omega_c) before
-// the K entries, L the Frechet derivative of exp at A = C / (4 + m) along
-// Omega: scaling by 2^-s (s from the largest column sum of |A|, down to 1/4),
-// Horner for exp(A') and its derivative along Omega / 2^s (Taylor degree 12,
-// as in expm), then s squarings (e, l) <- (e e, l e + e l).
+// Exponential form: as k_clover_insert with B_c <- L(A_c, B_c) before the K
+// entries, L the Frechet derivative of exp at A = C / (4 + m) along B: scaling
+// by 2^-s (s from the largest column sum of |A|, down to 1/4), Horner for
+// exp(A') and its derivative along B / 2^s (Taylor degree 12, as in the field
+// kernels), then s squarings (e, l) <- (e e, l e + e l).
 // NB = 2 d_R lanes per (site, chirality block): lane i holds row i of A,
 // Omega and of the iterates and reads the other rows from LDS at each matrix
 // product (one lane holding whole NB x NB matrices spills them to scratch).  64-lane blocks (one wavefront) hold MPB = 64 / NB matrices;
@@ -800,9 +1065,10 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
                                                            const cplx<double> *Ye, const cplx<double> *Yo,
                                                            const cplx<double> *__restrict__ clov,
                                                            const cplx<double> *__restrict__ F,
-                                                           cplx<double> *__restrict__ K, Geom g, SigmaBlocks S,
+                                                           double *__restrict__ K, Geom g, SigmaBlocks S,
                                                            double m0, double csw, double cdet) {
-  constexpr int NB = 2 * D, MPB = 64 / NB;
+  // both chirality blocks of a site in one 64-lane block: K sums over them
+  constexpr int NB = 2 * D, MPB = 64 / NB / 2 * 2;
   __shared__ cplx<double> se[MPB][NB][NB], sl[MPB][NB][NB];
   const size_t V = 2 * (size_t)g.Vh;
   const int mloc0 = (int)threadIdx.x / NB;
@@ -811,10 +1077,10 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
   const int i = lane_used ? (int)threadIdx.x - mloc * NB : 0;   // row of this lane
   const size_t m0g = (size_t)blockIdx.x * MPB + mloc;
   const bool valid = lane_used && m0g < 2 * V;
-  const size_t mg = m0g < 2 * V ? m0g : 2 * V - 1;
-  const int c = (int)(mg / V);
-  const size_t lex = mg - (size_t)c * V;
-  size_t r = lex;
+  const size_t mg = m0g < 2 * V ? m0g : 2 * V - 2 + (m0g & 1);
+  const int c = (int)(mg & 1);
+  const unsigned lex = (unsigned)(mg >> 1);
+  unsigned r = lex;
   const int z = (int)(r % g.Z); r /= g.Z;
   const int y = (int)(r % g.Y); r /= g.Y;
   const int x = (int)(r % g.X);
@@ -822,23 +1088,24 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
   const int par = (t + x + y + z) & 1;
   const size_t cb = lex >> 1;
   const int si = i / D, ai = i - si * D;   // row i = (spin si, colour ai) of the block
-  cplx<double> om[NB], a[NB];
+  cplx<double> om[NB], a[NB];   // row i of B and A
 #pragma unroll
   for (int j = 0; j < NB; ++j) om[j] = mk(0.0, 0.0);
   if (Xe) {
     const cplx<double> *X = par ? Xo : Xe, *Y = par ? Yo : Ye;
-    const cplx<double> xi = X[(size_t)((2 * c + si) * D + ai) * g.stride + cb];
+    const size_t oi = (size_t)((2 * c + si) * D + ai) * g.stride + cb;
+    const cplx<double> xi = X[oi], yi = Y[oi];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int sj = j / D, aj = j - sj * D;
-      const cplx<double> yj = Y[(size_t)((2 * c + sj) * D + aj) * g.stride + cb];
-      om[j] = mk(xi.re * yj.re + xi.im * yj.im, xi.im * yj.re - xi.re * yj.im);
+      const size_t oj = (size_t)((2 * c + sj) * D + aj) * g.stride + cb;
+      om[j] = cfma_conj(X[oj], yi, cfma_conj(Y[oj], xi, om[j]));
     }
   }
   if (cdet != 0.0 && par == 1) {
     const cplx<double> *Mi = clov + (size_t)(2 + c) * (NB * (NB + 1) / 2) * g.stride + cb;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) om[j] = om[j] + cdet * herm_entry(Mi, g.stride, NB, i, j);
+    for (int j = 0; j < NB; ++j) om[j] = om[j] + (2.0 * cdet) * herm_entry(Mi, g.stride, NB, i, j);
   }
   // row i of A = (i/4) c_sw sum_p S[p][c][s][t] F_p[a][b] / (4 + m)
   const double f = 0.25 * csw / (4.0 + m0);
@@ -881,7 +1148,7 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
     a[j] = sc * a[j];
     om[j] = sc * om[j];
   }
-  constexpr int KT = 12;   // as in expm
+  constexpr int KT = kTaylor;
   cplx<double> e[NB], l[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
@@ -943,23 +1210,48 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
       }
     __syncthreads();
   }
-  // Omega' = L(A, Omega): rows to LDS, then this matrix's K entries shared
-  // out over its NB lanes (S.v holds 2 sigma)
+  // B' = L(A, B): rows to LDS, then the K entries of the site shared out over
+  // the 2 NB lanes of its two matrices (S.v holds 2 sigma)
   if (lane_used)
 #pragma unroll
     for (int j = 0; j < NB; ++j) sl[mloc][i][j] = l[j];
   __syncthreads();
   if (valid) {
-    for (int idx = i; idx < 6 * D * D; idx += NB) {
+    const int ml = mloc & ~1;
+    for (int idx = c * NB + i; idx < 6 * D * D; idx += 2 * NB) {
       const int p = idx / (D * D), b = (idx / D) % D, a2 = idx % D;
+      if (b > a2) continue;
       cplx<double> acc = mk(0.0, 0.0);
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) acc = cfma(S.v[p][c][s][tt], sl[mloc][tt * D + b][s * D + a2], acc);
-      K[(((size_t)(c * 6 + p) * D + b) * D + a2) * V + lex] = 0.5 * acc;
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) acc = cfma(S.v[p][c2][s][tt], sl[ml + c2][tt * D + b][s * D + a2], acc);
+      double *k = K + (size_t)p * D * D * V + lex;
+      const int e = b == a2 ? b : herm_pair(D, b, a2);
+      k[(size_t)e * V] = 0.5 * acc.re;
+      if (b != a2) k[(size_t)(e + 1) * V] = 0.5 * acc.im;
     }
   }
+}
+
+// The Hermitian matrix `m` of a scratch array (K: m = plane; G: m = 4 plane +
+// leaf) at site xl from its n^2 stored reals.
+template <int N>
+__device__ __forceinline__ void herm_load(cplx<double> (&gm)[N][N], const double *G, int m, unsigned xl, size_t V) {
+  const double *gr = G + (size_t)__builtin_amdgcn_readfirstlane(m) * N * N * V;
+#pragma unroll
+  for (int i = 0; i < N; ++i) gm[i][i] = mk(*at(gr + (size_t)i * V, xl), 0.0);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = i + 1; j < N; ++j) {
+      const int e = herm_pair(N, i, j);
+      const double re = *at(gr + (size_t)e * V, xl), im = *at(gr + (size_t)(e + 1) * V, xl);
+      gm[i][j] = mk(re, im);
+      gm[j][i] = mk(re, -im);
+    }
 }
 
 // Thread per (plane p, site x): for the four leaves l of Q_p(x), the matrix
@@ -967,36 +1259,25 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
 // part of the pull-back of R(l) K_p, into G[p][k][N][N][V].
 template <int N, int REP>
 __global__ __launch_bounds__(64) void k_clover_leafgen(const cplx<double> *__restrict__ U,
-                                                       const cplx<double> *__restrict__ K,
-                                                       cplx<double> *__restrict__ G, Geom g) {
+                                                       const double *__restrict__ K,
+                                                       double *__restrict__ G, Geom g) {
   constexpr int D = rep_dim(N, REP);
   const size_t V = 2 * (size_t)g.Vh;
-  const size_t gid = (size_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  const unsigned gid = xcd_block(blockIdx.x, gridDim.x) * 64u + threadIdx.x;
   // 64-site chunks, the six planes of a chunk in consecutive wavefronts (the
   // planes that share a link direction read it close together in time)
-  const size_t chunk = gid / 384;
-  const int r6 = (int)(gid - chunk * 384);
-  const int p = r6 >> 6;
-  const size_t lex = chunk * 64 + (r6 & 63);
+  const unsigned chunk = gid / 384u;
+  const int r6 = (int)(gid - chunk * 384u);
+  const int p = __builtin_amdgcn_readfirstlane(r6 >> 6);
+  const unsigned lex = chunk * 64u + (r6 & 63);
   if (lex >= V) return;
   int mu, nu;
   plane_dirs(p, mu, nu);
-  size_t r = lex;
   int c[4];
-  c[3] = (int)(r % g.Z); r /= g.Z;
-  c[2] = (int)(r % g.Y); r /= g.Y;
-  c[1] = (int)(r % g.X);
-  c[0] = (int)(r / g.X);
+  lex_coords(g, lex, c);
   const PlaneNb pn(g, c, lex, mu, nu);
   cplx<double> Kh[D][D];
-  {
-    cplx<double> lam[D][D];
-    for (int b = 0; b < D; ++b)
-      for (int a = 0; a < D; ++a)
-        lam[b][a] = K[(((size_t)p * D + b) * D + a) * V + lex] + K[(((size_t)(6 + p) * D + b) * D + a) * V + lex];
-    for (int b = 0; b < D; ++b)
-      for (int a = 0; a < D; ++a) Kh[b][a] = mk(lam[b][a].re + lam[a][b].re, lam[b][a].im - lam[a][b].im);
-  }
+  herm_load<D>(Kh, K, p, lex, V);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     cplx<double> L[N][N];
@@ -1026,46 +1307,27 @@ __global__ __launch_bounds__(64) void k_clover_leafgen(const cplx<double> *__res
     double tr = 0.0;
     for (int i = 0; i < N; ++i) tr += Z[i][i].re;
     // g = (H - tr(H)/N) / 2, H = (Z + Z^+)/2, Hermitian: stored as N^2 reals
-    // (g_ii, then Re g_ij and Im g_ij for i < j), see g_load
-    double *gr = reinterpret_cast<double *>(G) + (size_t)(p * 4 + k) * N * N * V + lex;
+    // (g_ii, then Re g_ij and Im g_ij for i < j), see herm_load
+    double *gr = G + (size_t)(p * 4 + k) * N * N * V;
 #pragma unroll
-    for (int i = 0; i < N; ++i) gr[(size_t)i * V] = 0.5 * (Z[i][i].re - tr / N);
+    for (int i = 0; i < N; ++i) *at(gr + (size_t)i * V, lex) = 0.5 * (Z[i][i].re - tr / N);
     int t = N;
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
       for (int j = i + 1; j < N; ++j) {
-        gr[(size_t)t * V] = 0.25 * (Z[i][j].re + Z[j][i].re);
-        gr[(size_t)(t + 1) * V] = 0.25 * (Z[i][j].im - Z[j][i].im);
+        *at(gr + (size_t)t * V, lex) = 0.25 * (Z[i][j].re + Z[j][i].re);
+        *at(gr + (size_t)(t + 1) * V, lex) = 0.25 * (Z[i][j].im - Z[j][i].im);
         t += 2;
       }
   }
-}
-
-// The Hermitian leaf matrix g of (plane, leaf) p4k at site xl from its N^2
-// stored reals (k_clover_leafgen).
-template <int N>
-__device__ __forceinline__ void g_load(cplx<double> (&gm)[N][N], const cplx<double> *G, int p4k, size_t xl, size_t V) {
-  const double *gr = reinterpret_cast<const double *>(G) + (size_t)p4k * N * N * V + xl;
-#pragma unroll
-  for (int i = 0; i < N; ++i) gm[i][i] = mk(gr[(size_t)i * V], 0.0);
-  int t = N;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = i + 1; j < N; ++j) {
-      const double re = gr[(size_t)t * V], im = gr[(size_t)(t + 1) * V];
-      gm[i][j] = mk(re, im);
-      gm[j][i] = mk(re, -im);
-      t += 2;
-    }
 }
 
 // X <- S^+ X S for a Hermitian X, S a fundamental link (dag: its adjoint)
 // read from the structure-of-arrays copy; the upper triangle is formed and
 // mirrored, so X stays exactly Hermitian.
 template <int N>
-__device__ __forceinline__ void herm_transport(cplx<double> (&X)[N][N], const cplx<double> *Us, size_t V, size_t lex,
+__device__ __forceinline__ void herm_transport(cplx<double> (&X)[N][N], const cplx<double> *Us, size_t V, unsigned lex,
                                                int mu, bool dag) {
   cplx<double> S[N][N], T[N][N];
   load_link<N>(S, Us, V, lex, mu, dag);
@@ -1102,7 +1364,7 @@ __device__ __forceinline__ void herm_transport(cplx<double> (&X)[N][N], const cp
 // link at a forward step receives +H_J, at a backward one -S_J^+ H_J S_J.
 template <int N, int J>
 __device__ __forceinline__ void plaquette_horner(cplx<double> (&acc)[N][N], const cplx<double> *Us,
-                                                 const cplx<double> *Gl, size_t V, const PlaneNb &pn, int lo, int hi,
+                                                 const double *Gl, size_t V, const PlaneNb &pn, int lo, int hi,
                                                  int p, int za, int zb) {
   constexpr int ca[4] = {0, 1, 1, 0}, cb[4] = {0, 0, 1, 1};   // corner c_m - z
   constexpr int sa[4] = {0, 1, 0, 0}, sb[4] = {0, 0, 1, 0};   // start of the link of S_m - z
@@ -1110,14 +1372,14 @@ __device__ __forceinline__ void plaquette_horner(cplx<double> (&acc)[N][N], cons
 #pragma unroll
   for (int s = 1; s <= 3; ++s) {
     const int m = (J + s) & 3;
-    g_load<N>(gm, Gl, p * 4 + m, pn.at(za + ca[m], zb + cb[m]), V);
+    herm_load<N>(gm, Gl, p * 4 + m, pn.at(za + ca[m], zb + cb[m]), V);
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
       for (int j = 0; j < N; ++j) H[i][j] = s == 1 ? gm[i][j] : H[i][j] + gm[i][j];
     herm_transport<N>(H, Us, V, pn.at(za + sa[m], zb + sb[m]), (m & 1) ? hi : lo, m >= 2);
   }
-  g_load<N>(gm, Gl, p * 4 + J, pn.at(za + ca[J], zb + cb[J]), V);
+  herm_load<N>(gm, Gl, p * 4 + J, pn.at(za + ca[J], zb + cb[J]), V);
 #pragma unroll
   for (int i = 0; i < N; ++i)
 #pragma unroll
@@ -1130,26 +1392,22 @@ __device__ __forceinline__ void plaquette_horner(cplx<double> (&acc)[N][N], cons
 // (gradient), stored or accumulated.
 template <int N>
 __global__ __launch_bounds__(128) void k_clover_gather(const cplx<double> *__restrict__ U,
-                                                       const cplx<double> *__restrict__ Gl, double *P, Geom g,
+                                                       const double *__restrict__ Gl, double *P, Geom g,
                                                        double coef, int gradient, int accumulate) {
   const size_t V = 2 * (size_t)g.Vh;
-  const size_t gid = (size_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  const unsigned gid = xcd_block(blockIdx.x, gridDim.x) * 128u + threadIdx.x;
   // 64-site chunks, the four directions of a chunk in consecutive
   // wavefronts: the lanes of a wavefront hold one direction on consecutive
   // sites (coalesced structure-of-arrays link reads, the same planes in every
   // lane), and the two directions of a plane read its leaf matrices close
   // together in time
-  const size_t chunk = gid / 256;
-  const int r4 = (int)(gid - chunk * 256);
-  const int rho = r4 >> 6;
-  const size_t lex = chunk * 64 + (r4 & 63);
+  const unsigned chunk = gid / 256u;
+  const int r4 = (int)(gid & 255u);
+  const int rho = __builtin_amdgcn_readfirstlane(r4 >> 6);
+  const unsigned lex = chunk * 64u + (r4 & 63);
   if (lex >= V) return;
-  size_t r = lex;
   int cy[4];
-  cy[3] = (int)(r % g.Z); r /= g.Z;
-  cy[2] = (int)(r % g.Y); r /= g.Y;
-  cy[1] = (int)(r % g.X);
-  cy[0] = (int)(r / g.X);
+  lex_coords(g, lex, cy);
   // forward (af) and backward (ab) occurrences; the backward sum is
   // transported by the link itself once at the end
   cplx<double> af[N][N], ab[N][N];
@@ -1188,7 +1446,7 @@ __global__ __launch_bounds__(128) void k_clover_gather(const cplx<double> *__res
     for (int i = 0; i < N; ++i)
       for (int j = 0; j < N; ++j) Fo[i][j] = Gm[i][j];
   }
-  double *out = P + (lex * 4 + rho) * N * N * 2;
+  double *out = P + ((size_t)lex * 4 + rho) * N * N * 2;
   for (int i = 0; i < N; ++i)
     for (int j = 0; j < N; ++j) {
       double re = Fo[i][j].re, im = Fo[i][j].im;
@@ -1201,52 +1459,254 @@ __global__ __launch_bounds__(128) void k_clover_gather(const cplx<double> *__res
     }
 }
 
+// Fundamental representation: the link force without leaf matrices.  A leaf
+// whose loop starts at corner c_k passes the link as B U rest, and moving the
+// link moves Im tr[B U rest K_k] by Re tr[T U rest K_k B]: the link at step J
+// of the plaquette S_0 S_1 S_2 S_3 (see plaquette_horner) receives
+//   U R_J,   R_J = sum_k S_{J+1}..S_{k-1} K_k S_k..S_{J+3}   (k = J+1 .. J+4),
+// the sum over the corners of the plaquette, and a backward step, as U^+ in
+// the loop, -R_J U^+.  With a = S_{J+1}, A = a, M = K a each further corner is
+// M <- (M + A K) S, A <- A S: eight products for the four corners, and the
+// Hermitian traceless part is taken once, of the sum over the plaquettes.
+template <int N>
+__device__ __forceinline__ void herm_mac(cplx<double> (&M)[N][N], const cplx<double> (&A)[N][N],
+                                         const cplx<double> (&K)[N][N]) {   // M += A K, K Hermitian
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      cplx<double> s = rfma(K[j][j].re, A[i][j], M[i][j]);
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        if (q != j) s = cfma(A[i][q], K[q][j], s);
+      M[i][j] = s;
+    }
+}
+
+// off, not known before d is: loads from it are not issued earlier.  (The
+// compiler otherwise issues the loads of all steps at once, and spills.)
+__device__ __forceinline__ unsigned after(unsigned off, double d) {
+  asm volatile("" : "+v"(off) : "v"(d));
+  return off;
+}
+
+// R_J of one plaquette; the loads of a step are issued one step ahead.
+template <int N, int J>
+__device__ __forceinline__ void plaquette_corners(cplx<double> (&M)[N][N], const cplx<double> *Us, const double *K,
+                                                  size_t V, const PlaneNb &pn, int lo, int hi, int p, int za, int zb) {
+  constexpr int ca[4] = {0, 1, 1, 0}, cb[4] = {0, 0, 1, 1};   // corner c_m - z
+  constexpr int sa[4] = {0, 1, 0, 0}, sb[4] = {0, 0, 1, 0};   // start of the link of S_m - z
+  constexpr int m1 = (J + 1) & 3, m2 = (J + 2) & 3, m3 = (J + 3) & 3;
+  cplx<double> A[N][N], S2[N][N], k2[N][N], S3[N][N], k3[N][N], kJ[N][N];
+  load_link<N>(A, Us, V, pn.at(za + sa[m1], zb + sb[m1]), (m1 & 1) ? hi : lo, m1 >= 2);
+  herm_load<N>(M, K, p, pn.at(za + ca[m1], zb + cb[m1]), V);
+  load_link<N>(S2, Us, V, pn.at(za + sa[m2], zb + sb[m2]), (m2 & 1) ? hi : lo, m2 >= 2);
+  herm_load<N>(k2, K, p, pn.at(za + ca[m2], zb + cb[m2]), V);
+  mul_right<N>(M, A);
+  load_link<N>(S3, Us, V, after(pn.at(za + sa[m3], zb + sb[m3]), M[0][0].re), (m3 & 1) ? hi : lo, m3 >= 2);
+  herm_load<N>(k3, K, p, after(pn.at(za + ca[m3], zb + cb[m3]), M[0][0].re), V);
+  herm_mac<N>(M, A, k2);
+  mul_right<N>(M, S2);
+  mul_right<N>(A, S2);
+  herm_load<N>(kJ, K, p, after(pn.at(za + ca[J], zb + cb[J]), M[0][0].re), V);
+  herm_mac<N>(M, A, k3);
+  mul_right<N>(M, S3);
+  mul_right<N>(A, S3);
+  herm_mac<N>(M, A, kJ);
+}
+
+// Thread per link (y, rho) as k_clover_gather, with which it shares the order
+// of work; a block holds the four directions of 64 sites.  Bound by its loads
+// of neighbour links and K through L2 (19 links and 24 K a link) at two waves
+// per SIMD.  SU(3) FUND 24^4: 612 us with the leaf matrices, after 484 us to
+// make them (573 MB of scratch against K's 143 MB); 579 us from K.
+template <int N>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N <= 3 ? 2 : 1))) void k_clover_gather_fund(const cplx<double> *__restrict__ U,
+                                                            const double *__restrict__ K, double *P, Geom g,
+                                                            double coef, int gradient, int accumulate) {
+  __shared__ cplx<double> acc[2 * N * N][256];
+  const size_t V = 2 * (size_t)g.Vh;
+  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  const int rho = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const unsigned lex = b * 64u + (threadIdx.x & 63);
+  if (lex >= V) return;
+  int cy[4];
+  lex_coords(g, lex, cy);
+  // af, ab: the sums over the plaquettes that pass the link forward and
+  // backward, each thread's own in LDS (they leave room for the products)
+#pragma unroll
+  for (int e = 0; e < 2 * N * N; ++e) acc[e][threadIdx.x] = mk(0.0, 0.0);
+#pragma unroll 1
+  for (int q = 0; q < 8; ++q) {
+    const int nu = q & 3, back = q >> 2;
+    if (nu == rho) continue;
+    const int lo = rho < nu ? rho : nu, hi = rho < nu ? nu : rho;
+    const int p = lo == 0 ? hi - 1 : lo == 1 ? hi + 1 : 5;
+    const PlaneNb pn(g, cy, lex, lo, hi);
+    cplx<double> M[N][N];
+    if (rho == lo) {
+      if (!back) plaquette_corners<N, 0>(M, U, K, V, pn, lo, hi, p, 0, 0);   // S_0 of the plaquette at y
+      else plaquette_corners<N, 2>(M, U, K, V, pn, lo, hi, p, 0, -1);        // S_2 of the one at y - hi
+    } else {
+      if (!back) plaquette_corners<N, 1>(M, U, K, V, pn, lo, hi, p, -1, 0);  // S_1 of the one at y - lo
+      else plaquette_corners<N, 3>(M, U, K, V, pn, lo, hi, p, 0, 0);         // S_3 of the one at y
+    }
+    cplx<double>(*s)[256] = acc + back * N * N;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j) s[i * N + j][threadIdx.x] = s[i * N + j][threadIdx.x] + M[i][j];
+  }
+  // H: Hermitian part of Z = U af - ab U^+ (upper triangle)
+  cplx<double> H[N][N], u[N][N];
+  load_link<N>(u, U, V, lex, rho, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = i; j < N; ++j) {
+      cplx<double> s = mk(0.0, 0.0), t = s;   // Z_ij and Z_ji
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const cplx<double> bi = acc[N * N + i * N + q][threadIdx.x];
+        s = cfma(u[i][q], acc[q * N + j][threadIdx.x], s);
+        s = cfma_conj(u[j][q], mk(-bi.re, -bi.im), s);
+        if (j != i) {
+          const cplx<double> bj = acc[N * N + j * N + q][threadIdx.x];
+          t = cfma(u[j][q], acc[q * N + i][threadIdx.x], t);
+          t = cfma_conj(u[i][q], mk(-bj.re, -bj.im), t);
+        }
+      }
+      if (j == i) t = s;
+      H[i][j] = mk(0.5 * (s.re + t.re), 0.5 * (s.im - t.im));
+    }
+  // force = coef (H - tr(H)/N) / 2
+  double tr = 0.0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) tr += H[i][i].re;
+  cplx<double> Fo[N][N];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = i; j < N; ++j) {
+      Fo[i][j] = mk(0.5 * coef * (H[i][j].re - (i == j ? tr / N : 0.0)), 0.5 * coef * H[i][j].im);
+      if (j != i) Fo[j][i] = mk(Fo[i][j].re, -Fo[i][j].im);
+    }
+  if (gradient) {
+    cplx<double> Gm[N][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        cplx<double> s = mk(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < N; ++q) s = cfma(Fo[i][q], u[q][j], s);
+        Gm[i][j] = mk(-2.0 * s.im, 2.0 * s.re);
+      }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j) Fo[i][j] = Gm[i][j];
+  }
+  cplx<double> *out = reinterpret_cast<cplx<double> *>(P) + ((size_t)lex * 4 + rho) * N * N;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      cplx<double> v = Fo[i][j];
+      if (accumulate) v = v + out[i * N + j];
+      out[i * N + j] = v;
+    }
+}
+
 // log|det D_oo(x)| summed over the odd sites: thread per (odd site, block),
-// Gaussian elimination with partial pivoting of the stored inverse block
-// (log|det D_oo| = -log|det D_oo^{-1}|), block partial sums.
+// the block index fastest, Gaussian elimination with partial pivoting of the
+// stored inverse block (log|det D_oo| = -log|det D_oo^{-1}|) in registers (row
+// interchanges as selects, every index a compile-time constant), block partial
+// sums.  SU(3) FUND 24^4: 206 us with indexed rows, which went to scratch;
+// the whole call 233 us then, 57 us now.
 template <int D>
 __global__ __launch_bounds__(64) void k_clover_logdet(const cplx<double> *__restrict__ clov, double *partial,
                                                       Geom g) {
   constexpr int NB = 2 * D;
-  __shared__ double sh[1];
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned gid = blockIdx.x * 64u + threadIdx.x;
   double v = 0.0;
-  if (gid < 2 * (size_t)g.Vh) {
-    const int c = (int)(gid / g.Vh);
-    const size_t cb = gid - (size_t)c * g.Vh;
+  if (gid < 2 * (unsigned)g.Vh) {
+    const unsigned c = gid & 1, cb = gid >> 1;
     const cplx<double> *Mi = clov + (size_t)(2 + c) * (NB * (NB + 1) / 2) * g.stride + cb;
     cplx<double> a[NB][NB];
+#pragma unroll
     for (int i = 0; i < NB; ++i)
-      for (int j = 0; j < NB; ++j) a[i][j] = herm_entry(Mi, g.stride, NB, i, j);
+#pragma unroll
+      for (int j = i; j < NB; ++j) {
+        const cplx<double> m = Mi[(size_t)tri_index(NB, i, j) * g.stride];
+        a[i][j] = m;
+        if (j != i) a[j][i] = mk(m.re, -m.im);
+      }
     double ld = 0.0;
-    for (int col = 0; col < NB; ++col) {
-      int piv = col;
-      double best = a[col][col].re * a[col][col].re + a[col][col].im * a[col][col].im;
-      for (int rr = col + 1; rr < NB; ++rr) {
-        const double m2 = a[rr][col].re * a[rr][col].re + a[rr][col].im * a[rr][col].im;
-        if (m2 > best) {
-          best = m2;
-          piv = rr;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      int p = k;
+      double best = a[k][k].re * a[k][k].re + a[k][k].im * a[k][k].im;
+#pragma unroll
+      for (int r = k + 1; r < NB; ++r) {
+        const double m2 = a[r][k].re * a[r][k].re + a[r][k].im * a[r][k].im;
+        p = m2 > best ? r : p;
+        best = m2 > best ? m2 : best;
+      }
+      ld += 0.5 * log(best);
+#pragma unroll
+      for (int r = k + 1; r < NB; ++r) {
+        const bool sw = p == r;
+#pragma unroll
+        for (int j = k; j < NB; ++j) {
+          const cplx<double> tk = a[k][j], tr = a[r][j];
+          a[k][j] = sw ? tr : tk;
+          a[r][j] = sw ? tk : tr;
         }
       }
-      if (piv != col)
-        for (int j = 0; j < NB; ++j) {
-          const cplx<double> tmp = a[col][j];
-          a[col][j] = a[piv][j];
-          a[piv][j] = tmp;
-        }
-      ld += 0.5 * log(best);
-      const cplx<double> d = a[col][col];
       const double dn = 1.0 / best;
-      const cplx<double> di = mk(d.re * dn, -d.im * dn);
-      for (int rr = col + 1; rr < NB; ++rr) {
-        const cplx<double> fct = cmul(a[rr][col], di);
-        for (int j = col; j < NB; ++j) a[rr][j] = a[rr][j] - cmul(fct, a[col][j]);
+      const cplx<double> di = mk(a[k][k].re * dn, -a[k][k].im * dn);
+#pragma unroll
+      for (int r = k + 1; r < NB; ++r) {
+        const cplx<double> f = cmul(a[r][k], di);
+#pragma unroll
+        for (int j = k + 1; j < NB; ++j) a[r][j] = a[r][j] - cmul(f, a[k][j]);
       }
     }
     v = -ld;
   }
-  const double s = block_sum(v, sh);
+  const double s = wave_sum(v);
+  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
+// The same for larger blocks, NB lanes per matrix (rows_exchange), the 64
+// matrices of a block in turn.
+template <int D>
+__global__ __launch_bounds__(64) void k_clover_logdet_rows(const cplx<double> *__restrict__ clov, double *partial,
+                                                           Geom g) {
+  constexpr int NB = 2 * D, MPB = 64 / NB;
+  __shared__ cplx<double> sh[MPB][NB][NB + 1];
+  __shared__ int perm[MPB][NB];
+  const int mloc0 = (int)threadIdx.x / NB;
+  const bool lane_used = mloc0 < MPB;
+  const int mloc = lane_used ? mloc0 : MPB - 1;
+  const int i = lane_used ? (int)threadIdx.x - mloc * NB : 0;
+  const unsigned n = 2 * (unsigned)g.Vh;
+  double v = 0.0;
+  for (int m0 = 0; m0 < 64; m0 += MPB) {
+    const unsigned gid = blockIdx.x * 64u + m0 + mloc;
+    const bool valid = lane_used && m0 + mloc < 64 && gid < n;
+    const unsigned m = valid ? gid : 0;
+    const unsigned c = m & 1, cb = m >> 1;
+    const cplx<double> *Mi = clov + (size_t)(2 + c) * (NB * (NB + 1) / 2) * g.stride + cb;
+    cplx<double> w[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) w[j] = herm_entry(Mi, g.stride, NB, i, j);
+    int mine;
+    const double ld = rows_exchange<NB>(w, sh[mloc], perm[mloc], i, lane_used, mine);
+    if (valid && i == 0) v -= ld;
+  }
+  const double s = wave_sum(v);
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
@@ -1274,21 +1734,28 @@ static hipError_t clover_force_nr(void *P, const void *Xe, const void *Xo, const
       if (e != hipSuccess) return e;
     }
     const SigmaBlocks S = sigma_blocks();
-    const dim3 ig((unsigned)((2 * V + 63) / 64));
+    const dim3 ig((unsigned)((V + 63) / 64));
+    const cplx<double> *xe = (const cplx<double> *)Xe, *xo = (const cplx<double> *)Xo, *ye = (const cplx<double> *)Ye,
+                       *yo = (const cplx<double> *)Yo, *cl = (const cplx<double> *)clov, *u = (const cplx<double> *)U;
     if (expo) {
-      constexpr int MPB = 64 / (2 * D);
+      constexpr int MPB = 64 / (2 * D) / 2 * 2;
       const dim3 rg((unsigned)((2 * V + MPB - 1) / MPB));
-      hipLaunchKernelGGL((k_clover_insert_rows<D>), rg, dim3(64), 0, st, (const cplx<double> *)Xe,
-                         (const cplx<double> *)Xo, (const cplx<double> *)Ye, (const cplx<double> *)Yo,
-                         (const cplx<double> *)clov, (const cplx<double> *)F, (cplx<double> *)K, g, S, m0, csw, cdet);
-    } else
-      hipLaunchKernelGGL((k_clover_insert<D>), ig, dim3(64), 0, st, (const cplx<double> *)Xe,
-                         (const cplx<double> *)Xo, (const cplx<double> *)Ye, (const cplx<double> *)Yo,
-                         (const cplx<double> *)clov, (const cplx<double> *)F, (cplx<double> *)K, g, S, m0, csw, cdet);
-    hipLaunchKernelGGL((k_clover_leafgen<N, REP>), dim3((unsigned)(6 * ((V + 63) / 64))), dim3(64), 0, st,
-                       (const cplx<double> *)U, (const cplx<double> *)K, (cplx<double> *)Gl, g);
-    hipLaunchKernelGGL((k_clover_gather<N>), dim3((unsigned)(2 * ((V + 63) / 64))), dim3(128), 0, st,
-                       (const cplx<double> *)U, (const cplx<double> *)Gl, (double *)P, g, coef, gradient, accumulate);
+      hipLaunchKernelGGL((k_clover_insert_rows<D>), rg, dim3(64), 0, st, xe, xo, ye, yo, cl, (const cplx<double> *)F, K,
+                         g, S, m0, csw, cdet);
+    } else if (Xe) {
+      hipLaunchKernelGGL((k_clover_insert<D, false>), ig, dim3(64), 0, st, xe, xo, ye, yo, cl, K, g, S, cdet);
+    } else {
+      hipLaunchKernelGGL((k_clover_insert<D, true>), ig, dim3(64), 0, st, xe, xo, ye, yo, cl, K, g, S, cdet);
+    }
+    if constexpr (REP == 0) {
+      hipLaunchKernelGGL((k_clover_gather_fund<N>), ig, dim3(256), 0, st, u, K, (double *)P, g, coef, gradient,
+                         accumulate);
+    } else {
+      hipLaunchKernelGGL((k_clover_leafgen<N, REP>), dim3((unsigned)(6 * ((V + 63) / 64))), dim3(64), 0, st, u, K, Gl,
+                         g);
+      hipLaunchKernelGGL((k_clover_gather<N>), dim3((unsigned)(2 * ((V + 63) / 64))), dim3(128), 0, st, u, Gl,
+                         (double *)P, g, coef, gradient, accumulate);
+    }
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -1329,8 +1796,8 @@ hipError_t launch_clover_logdet(const void *clov, double *partial, const Geom &g
   switch (d) {
     case 2: hipLaunchKernelGGL(k_clover_logdet<2>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
     case 3: hipLaunchKernelGGL(k_clover_logdet<3>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
-    case 4: hipLaunchKernelGGL(k_clover_logdet<4>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
-    case 6: hipLaunchKernelGGL(k_clover_logdet<6>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
+    case 4: hipLaunchKernelGGL(k_clover_logdet_rows<4>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
+    case 6: hipLaunchKernelGGL(k_clover_logdet_rows<6>, grid, dim3(64), 0, st, (const cplx<double> *)clov, partial, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

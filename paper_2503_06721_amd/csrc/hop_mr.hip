@@ -61,18 +61,6 @@ __device__ __forceinline__ void split_halves(cplx<T> v, cplx<T> &lo, cplx<T> &hi
   split_halves(v.im, lo.im, hi.im);
 }
 
-// Element off of the array at base: base is the same for every lane of the
-// wavefront and the 32-bit offset is per lane, which selects global loads
-// and stores with a scalar base address and a single VGPR offset.
-template <typename V>
-__device__ __forceinline__ const V *at(const V *base, uint32_t off) {
-  return reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + off * (uint32_t)sizeof(V));
-}
-template <typename V>
-__device__ __forceinline__ V *at(V *base, uint32_t off) {
-  return reinterpret_cast<V *>(reinterpret_cast<char *>(base) + off * (uint32_t)sizeof(V));
-}
-
 // Per-block staging of the link entries of one hop.  The block's 64 K lanes
 // cover ROWS = K LPS entry rows of the TS-site tile per pass: wavefront w
 // stages rows LPS (w + p K) + rg, p < PER, at its own sites (the lane's

@@ -178,6 +178,18 @@ __host__ __device__ __forceinline__ size_t link_at(int pmu, int E, int stride, i
   return (size_t)pmu * E * stride + link_site(E, stride, i) + link_row(e, stride);
 }
 
+// Element off of the array at base: base is the same for every lane of the
+// wavefront and the 32-bit offset is per lane, which selects global loads
+// and stores with a scalar base address and a single VGPR offset.
+template <typename V>
+__device__ __forceinline__ const V *at(const V *base, uint32_t off) {
+  return reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + off * (uint32_t)sizeof(V));
+}
+template <typename V>
+__device__ __forceinline__ V *at(V *base, uint32_t off) {
+  return reinterpret_cast<V *>(reinterpret_cast<char *>(base) + off * (uint32_t)sizeof(V));
+}
+
 // ------------------------------------------------------------- reductions
 // Sum over a 64-lane wavefront (result valid in every lane).
 __device__ __forceinline__ double wave_sum(double v) {

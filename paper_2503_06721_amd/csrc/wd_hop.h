@@ -166,7 +166,7 @@ struct RStep {
     }
     const cplx<T> o = ld_nt(rin);
     const cplx<T> n = mk<T>((T)fma(-alpha, re, (double)o.re), (T)fma(-alpha, im, (double)o.im));
-    const cplx<T> w = act ? n : o;
+    const cplx<T> w = mk<T>(act ? n.re : o.re, act ? n.im : o.im);
     st_nt(r, w);
     return w;
   }

@@ -230,8 +230,8 @@ hipError_t launch_clover_field(void *clov, const void *U, double *F, double *Us,
 hipError_t launch_clover_apply(void *out, const void *in, const void *clov, const Geom &g, int d, int parity,
                                int nrhs, int prec, hipStream_t st);
 // Clover contribution to the link force of a functional with variation
-// -2 Re sum_x tr[dM Omega], Omega = X Y^+ (Xe non-null) + cdet D_oo^{-1} on odd
-// sites; P (+)= coef * force (or its gradient form).  F: 6 d^2 V, K: 12 d^2 V,
+// -2 Re sum_x tr[dM Omega], Omega = X Y^+ (Xe non-null) or cdet D_oo^{-1} on odd
+// sites (Xe NULL); P (+)= coef * force (or its gradient form).  F: 6 d^2 V, K: 12 d^2 V,
 // Gl: 24 N^2 V complex FP64 scratch (F only for the exponential form), Us:
 // 4 N^2 V complex FP64 (structure-of-arrays copy of the links).
 hipError_t launch_clover_force(void *P, const void *Xe, const void *Xo, const void *Ye, const void *Yo, const void *U,
