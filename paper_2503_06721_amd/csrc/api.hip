@@ -511,6 +511,9 @@ int wdirac_create_batch(wdirac_ctx **ctx, int Ng, int rep, const wdirac_geom *ge
     g.stride = (g.Vh + 255) & ~255;
     if (g.stride % 1024 == 0) g.stride += 256;
     for (int mu = 0; mu < 4; ++mu) g.bc[mu] = geoms[l].bc[mu];
+    g.dX.set(g.X);
+    g.dY.set(g.Y);
+    g.dZ.set(g.Z);
     c->spre[l + 1] = c->spre[l] + g.stride;
     c->vpre[l + 1] = c->vpre[l] + V;
   }

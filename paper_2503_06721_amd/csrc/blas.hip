@@ -213,6 +213,21 @@ __global__ __launch_bounds__(BT) void k_cg_update_xp(cplx<T> *__restrict__ x, cp
                                                      double delta, int per, FieldShape f) {
   const int sy = blockIdx.y;
   CgScalars &s = S[sy];
+  const int i = blockIdx.x * BT + threadIdx.x;
+  const bool in = i < f.vh[sy];
+  const size_t st = f.stride[sy];
+  const size_t base = (size_t)f.off[sy] + i + (size_t)blockIdx.z * per * st;
+  cplx<T> pv[4], xv[4], rv[4];
+  const auto load = [&](int c) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const size_t o = base + (size_t)(c + k) * st;
+      pv[k] = p[o];
+      xv[k] = x[o];
+      rv[k] = r[o];
+    }
+  };
+  if (in) load(0);   // on their way while the partial sums are added up
   if (!s.act_it) return;
   const double a = s.alpha, rho = s.rho_it;
   double rr;
@@ -222,21 +237,10 @@ __global__ __launch_bounds__(BT) void k_cg_update_xp(cplx<T> *__restrict__ x, cp
   } else {
     rr = s.rr;
   }
+  if (!in) return;
   const bool ok = isfinite(rr);
-  const int i = blockIdx.x * BT + threadIdx.x;
-  if (i >= f.vh[sy]) return;
   const double b = rr / rho;
-  const size_t st = f.stride[sy];
-  const size_t base = (size_t)f.off[sy] + i + (size_t)blockIdx.z * per * st;
-  for (int c = 0; c < per; c += 4) {
-    cplx<T> pv[4], xv[4], rv[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const size_t o = base + (size_t)(c + k) * st;
-      pv[k] = p[o];
-      xv[k] = x[o];
-      rv[k] = r[o];
-    }
+  for (int c = 0;;) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const size_t o = base + (size_t)(c + k) * st;
@@ -245,6 +249,9 @@ __global__ __launch_bounds__(BT) void k_cg_update_xp(cplx<T> *__restrict__ x, cp
       if (ok)
         p[o] = mk<T>((T)fma(b, (double)pv[k].re, (double)rv[k].re), (T)fma(b, (double)pv[k].im, (double)rv[k].im));
     }
+    c += 4;
+    if (c >= per) return;
+    load(c);
   }
 }
 

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
   if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
-  const int q = w / ngroups, grp = w - q * ngroups;
+  const int q = ngroups == 1 ? w : w / ngroups, grp = w - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
   const Geom g = a.lat[l].g;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
         const cplx<T> xv = ld_nt(xa + o);
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = step(rf + o, ri + o, ps + o, v);
+        const cplx<T> rn = step(rf + o, ld_nt(ri + o), ps + o, v);
         nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
   } else if (a.xadd) {
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
   if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int w = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
-  const int q = w / ngroups, grp = w - q * ngroups;
+  const int q = ngroups == 1 ? w : w / ngroups, grp = w - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
   const Geom g = a.lat[l].g;
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * D) __attribute__((amdgpu_waves_per_eu(W))) voi
         const cplx<T> xv = ld_nt(xa + o);
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = step(rf + o, ri + o, ps + o, v);
+        const cplx<T> rn = step(rf + o, ld_nt(ri + o), ps + o, v);
         nrm[k] += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
     }

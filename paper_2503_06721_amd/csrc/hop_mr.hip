@@ -258,11 +258,11 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
   if ((int)blockIdx.x < a.lead) return hop_lead(a);
   const int ngroups = a.ngroups;
   const int wi = tile_of_block(blockIdx.x - a.lead, a.ntiles * ngroups, a.xcd_remap);
-  const int q = wi / ngroups, grp = wi - q * ngroups;
+  const int q = ngroups == 1 ? wi : wi / ngroups, grp = wi - q * ngroups;
   const int tile = tile_order(q, a);
   const int l = lattice_of_tile(a, tile);
   const Geom g = a.lat[l].g;
-  const int tl = tile - a.lat[l].tile0;
+  const int tl = tile - a.lat[l].tile0;   // tile within its lattice
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wavefront = right-hand side
   const int rg = LPS == 2 ? lane >> 5 : 0;           // row group of this lane
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(64 * K) __attribute__((amdgpu_waves_per_eu(W))) voi
         const cplx<T> xv = ld_nt(at(xa + row, ooff));
         v.re = fma(ca, xv.re, v.re);
         v.im = fma(ca, xv.im, v.im);
-        const cplx<T> rn = step(at(rf + row, ooff), at(ri + row, ooff), at(ps + row, ooff), v);
+        const cplx<T> rn = step(at(rf + row, ooff), ld_nt(at(ri + row, ooff)), at(ps + row, ooff), v);
         nrm += (double)rn.re * rn.re + (double)rn.im * rn.im;
       }
   } else if (a.xadd) {

@@ -115,23 +115,35 @@ __host__ __device__ constexpr int RECON_PH(int mu, int sig, int r) {
 }
 
 // ---------------------------------------------------------------- geometry
+// Division of n < 2^31 by a fixed d >= 1: q = (hi(n m) + n) >> s with
+// s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1 (Granlund and Montgomery).
+struct FastDiv {
+  uint32_t m, s;
+  __host__ void set(uint32_t d) {
+    s = 0;
+    while ((1ull << s) < d) ++s;
+    m = (uint32_t)((((1ull << s) - d) << 32) / d + 1);
+  }
+  __device__ __forceinline__ uint32_t div(uint32_t n) const { return (__umulhi(n, m) + n) >> s; }
+};
+
 struct Geom {
   int T, X, Y, Z;   // extents, all even
   int Vh;           // sites per parity
   int stride;       // padded site count of one packed component row
   int bc[4];
+  FastDiv dX, dY, dZ;
 };
 
 // Coordinates of the site with index i among the sites of parity p.  With Z
 // even, that site has lexicographic index 2i or 2i+1 and both share t, x, y.
 __device__ __forceinline__ void cb_coords(const Geom &g, int i, int p, int &t, int &x, int &y, int &z) {
-  int lex0 = 2 * i;
-  int z0 = lex0 % g.Z;
-  int r = lex0 / g.Z;
-  y = r % g.Y;
-  r /= g.Y;
-  x = r % g.X;
-  t = r / g.X;
+  const uint32_t lex0 = 2 * (uint32_t)i;
+  const uint32_t r = g.dZ.div(lex0), q = g.dY.div(r);
+  const int z0 = (int)(lex0 - r * (uint32_t)g.Z);
+  y = (int)(r - q * (uint32_t)g.Y);
+  t = (int)g.dX.div(q);
+  x = (int)q - t * g.X;
   z = z0 + ((t + x + y + p) & 1);
 }
 __device__ __forceinline__ int cb_index(const Geom &g, int t, int x, int y, int z) {

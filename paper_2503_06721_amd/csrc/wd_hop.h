@@ -148,8 +148,8 @@ __device__ __forceinline__ void hop_lead(const HopArgs &a) {
 }
 
 // Residual update in the epilogue of a hop (HopArgs::r), element by element:
-// v = (A p) there, r = rin - alpha (v + sigma ps) in FP64, rounded to T as
-// stored.  Returns the stored value; an inactive system keeps rin.
+// v = (A p) there, o = rin, r = rin - alpha (v + sigma ps) in FP64, rounded to
+// T as stored.  Returns the stored value; an inactive system keeps rin.
 template <typename T>
 struct RStep {
   double alpha, sigma;
@@ -157,14 +157,13 @@ struct RStep {
   __device__ __forceinline__ RStep(const HopArgs &a, int sys)
       : alpha(a.sc ? a.sc[sys].alpha : 1.0), sigma(a.sigma), act(a.sc ? a.sc[sys].act_it != 0 : true),
         shifted(a.ps != nullptr) {}
-  __device__ __forceinline__ cplx<T> operator()(cplx<T> *r, const cplx<T> *rin, const cplx<T> *ps, cplx<T> v) const {
+  __device__ __forceinline__ cplx<T> operator()(cplx<T> *r, cplx<T> o, const cplx<T> *ps, cplx<T> v) const {
     double re = v.re, im = v.im;
     if (shifted) {
       const cplx<T> q = ld_nt(ps);
       re = fma(sigma, (double)q.re, re);
       im = fma(sigma, (double)q.im, im);
     }
-    const cplx<T> o = ld_nt(rin);
     const cplx<T> n = mk<T>((T)fma(-alpha, re, (double)o.re), (T)fma(-alpha, im, (double)o.im));
     const cplx<T> w = mk<T>(act ? n.re : o.re, act ? n.im : o.im);
     st_nt(r, w);
