@@ -1094,7 +1094,12 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
   const int check = ctx->cg_check_every;
   int rc = WDIRAC_OK;
   int launched = 0;   // iterations launched since start
-  bool use_graph = ctx->cg_graph && st == ctx->own;
+  // lattices that fit one workgroup iterate inside one kernel until they stop
+  // (mixed mode: from check to check, where replacements are decided)
+  const bool tiny = ctx->nlat == 1 && !clov64 && wd::cg_tiny_ok(ctx->g[0], ctx->d, ctx->real);
+  constexpr int kTinyIters = 512;
+  int seen_iters = 0;   // hops counted so far (tiny)
+  bool use_graph = ctx->cg_graph && st == ctx->own && !tiny;
   hipGraphExec_t exec = nullptr;
   for (;;) {
     WD_HIP(hipMemcpyAsync(hs.data(), w.sc, ns * sizeof(wd::CgScalars), hipMemcpyDeviceToHost, st));
@@ -1110,6 +1115,10 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
     }
     int max_iters = 0;
     for (int k = 0; k < ns; ++k) max_iters = std::max(max_iters, hs[k].iters);
+    if (tiny) {
+      hop_count += 4 * (max_iters - seen_iters);
+      seen_iters = max_iters;
+    }
     if (any_update && all_ready) {
       // residual replacement in FP64 (verifies convergence of the recursion)
       if (mixed) WD_HIP(wd::launch_accum_x(x, w.x32, f, st));
@@ -1126,7 +1135,12 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
       rc = WDIRAC_ENOCONV;
       break;
     }
-    const int nit = std::min(check, std::max(1, maxit - max_iters));
+    const int nit = std::min(tiny && !mixed ? kTinyIters : check, std::max(1, maxit - max_iters));
+    if (tiny) {
+      const double m4 = (4.0 + m0) * (4.0 + m0);
+      WD_HIP(wd::launch_cg_tiny(xi, p, r, UR, ctx->g[0], ctx->d, ctx->real, w.sc, m4, delta, nit, nrhs, prec, st));
+      continue;
+    }
     auto launch_iters = [&](int n) -> int {
       for (int it = 0; it < n; ++it) {
         wd::Counts cnt{};

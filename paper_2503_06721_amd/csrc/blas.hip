@@ -203,8 +203,8 @@ __global__ __launch_bounds__(1024) void k_cg_end(CgScalars *S, const double *__r
 // apart; 8192, 32^4 FP32: 47.1 against 40.9 + 5.5 us).
 // Thread per site and, by blockIdx.z, group of `per` components: all 4 d of
 // them where the sites alone give every CU four blocks, else four, which
-// shortens the chain of loads of a small lattice (SU(2) ADJ 32x16^3: 15.1 us,
-// the separate updates 23.6; SU(2) FUND 4^4: 3.7, they 7.9).
+// shortens the chain of loads of a small lattice (SU(2) ADJ 32x16^3: 13.0 us,
+// the separate updates 23.6; SU(2) FUND 4^4: 3.5, they 7.9).
 constexpr int kOwnSum = 4096;
 template <typename T, bool OWN>
 __global__ __launch_bounds__(BT) void k_cg_update_xp(cplx<T> *__restrict__ x, cplx<T> *__restrict__ p,

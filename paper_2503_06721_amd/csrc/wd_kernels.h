@@ -197,6 +197,12 @@ hipError_t launch_convert(void *out, int prec_out, const void *in, int prec_in, 
 // (rows of prow); x, p, r in prec.  Also the state update of the iteration.
 hipError_t launch_cg_update_xp(void *x, void *p, const void *r, CgScalars *s, const double *rr_partial, int prow,
                                const Counts &counts, double delta, const FieldShape &f, int prec, hipStream_t st);
+// cg_tiny.hip: up to nit iterations of every system of a small single lattice
+// (Vh d_R sites and colours in one workgroup) in one launch, until a system
+// stops; x, p, r packed even fields, one block per rhs.
+bool cg_tiny_ok(const Geom &g, int d, int real);
+hipError_t launch_cg_tiny(void *x, void *p, void *r, const void *links, const Geom &g, int d, int real, CgScalars *s,
+                          double m4, double delta, int nit, int nrhs, int prec, hipStream_t st);
 // With set_b2: b2 = sum(partial), stop2 = tol^2 b2, counters reset.  Otherwise
 // rho = sum(partial) for a freshly computed FP64 residual, and every system
 // that is neither converged nor broken down is (re)activated.
