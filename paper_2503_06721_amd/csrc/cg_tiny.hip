@@ -8,10 +8,11 @@
 // registers; x, p, u = D-hat p and the odd fields are in LDS (64 KB FP32,
 // 128 KB FP64), links come from L2 ahead of the barrier of their hop.  A solve
 // to 1e-10, per iteration (launched: 36 us SU(2), 48 to 100 us with 12 rhs):
-// SU(2) FUND 4^4 12.6 us, SU(3) FUND 19, SU(2) ADJ 20, SU(4) FUND 30, and 5%
-// more with 12 rhs, now bound by the LDS reads (8 d spinors per thread and hop)
-// and, d = 4, registers (115 spilled).  Larger lattices fill the LDS or the
-// registers of one CU and go back to one launch per hop.
+// SU(2) FUND 4^4 12.6 us, SU(3) FUND 17.4, SU(2) ADJ 16.3, SU(4) FUND 22.4, and
+// 5 to 13% more with 12 rhs, now bound by the LDS reads (8 d spinor components
+// per thread and hop).  Larger lattices fill the LDS or the registers of one CU
+// and go back to one launch per hop.  (Twice the threads, each half of them with
+// half of the directions: 11.8 us SU(2) 4^4, but 22 to 34 us for the others.)
 #include "wd_common.h"
 #include "wd_hop.h"
 #include "wd_kernels.h"
@@ -58,7 +59,8 @@ __device__ __forceinline__ void tiny_dir(cplx<T> (&acc)[4], const cplx<T> *in,
 // issues all of a hop's reads first: 8 d spinor components, all spilled).
 template <typename T>
 __device__ __forceinline__ void tiny_next(cplx<T> (&acc)[4], int &j) {
-  asm volatile("" : "+v"(acc[0].re), "+v"(acc[1].re), "+v"(acc[2].re), "+v"(acc[3].re), "+v"(j));
+#pragma unroll
+  for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(j) : "v"(acc[s].re), "v"(acc[s].im));
 }
 
 // acc = -2 H in for the thread's site of parity PAR and colour row; the links
