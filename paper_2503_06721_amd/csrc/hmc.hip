@@ -8,234 +8,151 @@
 //  * the link update U <- exp(i eps pi) U and the kinetic term sum tr(pi^2).
 #include "wd_common.h"
 #include "wd_kernels.h"
+#include "wd_links.h"
 
 namespace wd {
 
+// F = scale * (beta/N) (B - tr B/N)/2 (+ F) per link.  A block takes 16
+// consecutive sites; thread = column c (one per wavefront), direction mu, site.
+// The links that the staples of the tile have in common go through LDS (44 a
+// site, where the staples have 72), in three phases: the sites x-nu, whose
+// products with a column stay in registers, the corners x+mu-nu that close the
+// lower staples, and x with x+nu.  SU(3) 24^4: 493 us with a lane reading its
+// own links; 404 us with a direction of 64 sites per wavefront and each staple's
+// three links staged, 6.6 GB through L2 at 16 TB/s, half of every line unused;
+// 355 us from this tile with a thread per link, 2.8 GB but four wavefronts a
+// CU; 289 us.
 template <int N>
-struct Mat {
-  cplx<double> a[N][N];
-};
-
-template <int N>
-__device__ __forceinline__ Mat<N> ld_mat(const cplx<double> *p, bool dag) {
-  Mat<N> m;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const cplx<double> v = p[dag ? j * N + i : i * N + j];
-      m.a[i][j] = dag ? mk(v.re, -v.im) : v;
-    }
-  return m;
-}
-
-template <int N>
-__device__ __forceinline__ Mat<N> dagger(const Mat<N> &x) {
-  Mat<N> r;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = 0; j < N; ++j) r.a[i][j] = mk(x.a[j][i].re, -x.a[j][i].im);
-  return r;
-}
-
-template <int N>
-__device__ __forceinline__ Mat<N> mul(const Mat<N> &x, const Mat<N> &y) {
-  Mat<N> r;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      cplx<double> s = mk(0.0, 0.0);
-#pragma unroll
-      for (int k = 0; k < N; ++k) s = cfma(x.a[i][k], y.a[k][j], s);
-      r.a[i][j] = s;
-    }
-  return r;
-}
-
-// Links of the 64 lanes of a wavefront, staged through LDS.  A lane reading its
-// own N^2 entries from the canonical layout touches a cache line of its own
-// with every load: 64 lines a load, the bound of these kernels before.  Here
-// consecutive lanes fetch consecutive entries (lane's flat index k 64 + lane =
-// entry f % N^2 of the link of lane f / N^2), directly into LDS, where each
-// lane then finds its link (N^2 16-byte entries in a row).
-template <int N>
-struct LinkStage {
-  static constexpr int E = N * N, ELEMS = 64 * E;   // entries of one buffer
-  // buf <- link (site, mu) of every lane (32-bit site index)
-  static __device__ __forceinline__ void fetch(cplx<double> *buf, const cplx<double> *U, unsigned site, int mu) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const int f = k * 64 + lane, m = f / E, e = f - m * E;
-      const unsigned s = (unsigned)__shfl((int)site, m, 64);
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void *)(U + ((size_t)s * 4 + mu) * E + e),
-          (__attribute__((address_space(3))) void *)(buf + k * 64), 16, 0, 0);
-    }
-  }
-  static __device__ __forceinline__ Mat<N> read(const cplx<double> *buf, bool dag) {
-    return ld_mat<N>(buf + (threadIdx.x & 63) * E, dag);
-  }
-};
-// The loads of fetch() have landed (the caller's barrier makes them visible).
-__device__ __forceinline__ void wait_fetch() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-
-// Coordinates of lexicographic site lex, and the site one step away along mu.
-struct Site {
-  int c[4];
-  unsigned lex;
-  __device__ __forceinline__ Site(const Geom &g, unsigned l) : lex(l) {
-    unsigned r = l;
-    c[3] = (int)(r % (unsigned)g.Z); r /= (unsigned)g.Z;
-    c[2] = (int)(r % (unsigned)g.Y); r /= (unsigned)g.Y;
-    c[1] = (int)(r % (unsigned)g.X);
-    c[0] = (int)(r / (unsigned)g.X);
-  }
-  __device__ __forceinline__ int shift(const Geom &g, int mu, int step) const {   // difference of site indices
-    const int st = mu == 0 ? g.X * g.Y * g.Z : mu == 1 ? g.Y * g.Z : mu == 2 ? g.Z : 1;
-    const int L = mu == 0 ? g.T : mu == 1 ? g.X : mu == 2 ? g.Y : g.Z;
-    const int x = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
-    const int q = x + step, d = q < 0 ? step + L : q >= L ? step - L : step;
-    return d * st;
-  }
-};
-
-// Block index such that each XCD runs one contiguous range of blocks.
-__device__ __forceinline__ unsigned xcd_range(unsigned b, unsigned n) {
-  const unsigned q = n >> 3, rmd = n & 7, x = b & 7, j = b >> 3;
-  return x * q + (x < rmd ? x : rmd) + j;
-}
-
-// F = scale * (beta/N) (B - tr B/N)/2 (+ F) per link.  One wavefront per block:
-// 64 consecutive sites and one direction mu, the four directions of 64 sites
-// in consecutive blocks of one XCD.  The three links of a staple are staged
-// while the staple before is multiplied.  SU(3) 24^4: 493 us with a lane
-// reading its own links, 406 us; bound by the latency of the staged loads (19 a
-// link, 27 KB of LDS a wavefront, five wavefronts a CU).
-template <int N>
-__global__ __launch_bounds__(64) void k_gauge_force(const cplx<double> *__restrict__ U, cplx<double> *F, Geom g,
-                                                    double beta, double scale, int accumulate) {
-  using LS = LinkStage<N>;
-  __shared__ cplx<double> buf[3][LS::ELEMS];
-  const unsigned V = 2 * (unsigned)g.Vh;
+__global__ __launch_bounds__(64 * N) void k_gauge_force(const cplx<double> *__restrict__ U, cplx<double> *F, Geom g,
+                                                        double beta, double scale, int accumulate) {
+  using LT = LinkTile<N, 16, 64 * N>;
+  constexpr int E = N * N;
+  __shared__ cplx<double> buf[LT::elems(16)];
+  __shared__ unsigned tab[(16 + 12 + 16) * 16];
   const unsigned b = xcd_range(blockIdx.x, gridDim.x);
-  const int mu = (int)(b & 3), lane = threadIdx.x;
-  const unsigned lex = (b >> 2) * 64 + lane;
-  const Site x(g, lex < V ? lex : V - 1);   // lanes past the end repeat the last site and store nothing
-  const unsigned xp = x.lex + x.shift(g, mu, 1);
-  Mat<N> A;
+  const int c = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int mu = (int)(threadIdx.x >> 4) & 3, s = (int)(threadIdx.x & 15);
+  // slots: 4 nu + a: U_a(x-nu) | 3 mu + j: U_nu(x+mu-nu), nu the j-th other than mu
+  // | a: U_a(x), 4 + 3 b + j: U_a(x+b), a the j-th other than b
+  unsigned *t0 = tab, *t1 = tab + 16 * 16, *t2 = tab + 28 * 16;
+  if (c == 0) {
+    const Site x(g, b * 16 + s);
+    const unsigned xp = x.lex + x.shift(g, mu, 1), xm = x.lex + x.shift(g, mu, -1);
+    t2[mu * 16 + s] = x.lex * 4 + mu;
 #pragma unroll
-  for (int i = 0; i < N; ++i)
+    for (int j = 0; j < 3; ++j) {
+      const int nu = j + (j >= mu);
+      t1[(3 * mu + j) * 16 + s] = (xp + x.shift(g, nu, -1)) * 4 + nu;
+      t2[(4 + 3 * mu + j) * 16 + s] = xp * 4 + nu;
+    }
 #pragma unroll
-    for (int j = 0; j < N; ++j) A.a[i][j] = mk(0.0, 0.0);
-  // staple s: direction nu = the (s / 2)-th other than mu, upper (s even):
-  //   U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-  // lower: U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
-  const auto stage = [&](int s) {
-    const int nu = (s >> 1) + ((s >> 1) >= mu), low = s & 1;
-    const int d = x.shift(g, nu, low ? -1 : 1);
-    LS::fetch(buf[0], U, low ? xp + d : xp, nu);
-    LS::fetch(buf[1], U, x.lex + d, mu);
-    LS::fetch(buf[2], U, low ? x.lex + d : x.lex, nu);
-  };
-  stage(0);
-#pragma unroll 1
-  for (int s = 0; s < 6; ++s) {
-    wait_fetch();
-    __syncthreads();
-    const bool low = s & 1;
-    Mat<N> l0 = LS::read(buf[0], false), l2 = LS::read(buf[2], false);
-    const Mat<N> l1 = LS::read(buf[1], true);
-    __syncthreads();
-    if (s < 5) stage(s + 1);
-    else LS::fetch(buf[0], U, x.lex, mu);
-    if (low) l0 = dagger(l0);
-    else l2 = dagger(l2);
-    const Mat<N> m = mul<N>(mul<N>(l0, l1), l2);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int j = 0; j < N; ++j) A.a[i][j] = A.a[i][j] + m.a[i][j];
+    for (int a = 0; a < 4; ++a) t0[(4 * mu + a) * 16 + s] = xm * 4 + a;
   }
+  __syncthreads();
+  LT::template fetch<16>(buf, U, t0);
   wait_fetch();
   __syncthreads();
-  const Mat<N> M = mul<N>(LS::read(buf[0], false), A);
-  // B = (M - M^+)/(2i): B_ij = (M_ij - conj(M_ji)) / (2i)
-  double trB = 0.0;
+  // lower staples U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
+  Vec<N> v[3], A;
 #pragma unroll
-  for (int i = 0; i < N; ++i) trB += M.a[i][i].im;
-  const double c = scale * beta / N * 0.5;
-  cplx<double> *own = buf[1] + lane * LS::E;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const double re = M.a[i][j].re - M.a[j][i].re, im = M.a[i][j].im + M.a[j][i].im;
-      own[i * N + j] = mk(c * (0.5 * im - (i == j ? trB / N : 0.0)), c * (-0.5 * re));
-    }
+  for (int j = 0; j < 3; ++j) {
+    const int nu = j + (j >= mu);
+    v[j] = mulv_dag<N>(LT::at(buf, 4 * nu + mu, s), col<N>(LT::at(buf, 4 * nu + nu, s), c));
+  }
   __syncthreads();
-  const unsigned n = V - (b >> 2) * 64 < 64 ? V - (b >> 2) * 64 : 64;   // links of this block
+  LT::template fetch<12>(buf, U, t1);
+  wait_fetch();
+  __syncthreads();
+  A = mulv_dag<N>(LT::at(buf, 3 * mu, s), v[0]);
+  add<N>(A, mulv_dag<N>(LT::at(buf, 3 * mu + 1, s), v[1]));
+  add<N>(A, mulv_dag<N>(LT::at(buf, 3 * mu + 2, s), v[2]));
+  __syncthreads();
+  LT::template fetch<16>(buf, U, t2);
+  wait_fetch();
+  __syncthreads();
+  // upper staples U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
 #pragma unroll
-  for (int k = 0; k < LS::E; ++k) {
-    const unsigned f = k * 64 + lane, m = f / LS::E, e = f - m * LS::E;
-    if (m < n) {
-      cplx<double> *out = F + (((size_t)(b >> 2) * 64 + m) * 4 + mu) * LS::E + e;
-      cplx<double> v = buf[1][f];
-      if (accumulate) v = v + *out;
-      *out = v;
-    }
+  for (int j = 0; j < 3; ++j) {
+    const int nu = j + (j >= mu);
+    add<N>(A, mulv<N>(LT::at(buf, 4 + 3 * mu + j, s),
+                      mulv_dag<N>(LT::at(buf, 4 + 3 * nu + mu - (mu > nu), s), col_dag<N>(LT::at(buf, nu, s), c))));
+  }
+  const Vec<N> M = mulv<N>(LT::at(buf, mu, s), A);
+  __syncthreads();
+  // column c of M to LDS, row (s, mu) of ROW entries
+#pragma unroll
+  for (int i = 0; i < N; ++i) buf[(s * 4 + mu) * LT::ROW + i * N + c] = M.a[i];
+  __syncthreads();
+  // B = (M - M^+)/(2i): B_ij = (M_ij - conj(M_ji)) / (2i)
+  const double w = scale * beta / N * 0.5;
+  cplx<double> *out = F + (size_t)b * 64 * E;
+#pragma unroll
+  for (int f = threadIdx.x; f < 64 * E; f += 64 * N) {
+    const int m = f / E, e = f - m * E, i = e / N, j = e - i * N;
+    const cplx<double> *r = buf + m * LT::ROW;
+    const double re = r[i * N + j].re - r[j * N + i].re, im = r[i * N + j].im + r[j * N + i].im;
+    double trB = 0.0;
+    if (i == j)
+#pragma unroll
+      for (int k = 0; k < N; ++k) trB += r[k * N + k].im;
+    cplx<double> o = mk(w * (0.5 * im - trB / N), w * (-0.5 * re));
+    if (accumulate) o = o + out[f];
+    out[f] = o;
   }
 }
 
 // Sum over the sites of Re tr P_mu,nu / N over the six planes; a partial sum
-// per block of 64 sites, whose three wavefronts take two planes each.  tr P =
-// sum_ij a_ij conj(b_ij), a = U_mu(x) U_nu(x+mu), b = U_nu(x) U_mu(x+nu), links
-// staged as above.  SU(3) 24^4: 336 us before, 116 us.
+// per block of 64 sites, which it takes in two tiles of 32, a thread per (plane,
+// site).  tr P = sum_ij a_ij conj(b_ij), a = U_mu(x) U_nu(x+mu), b = U_nu(x)
+// U_mu(x+nu), the 16 links of a site staged once for its planes.  SU(3) 24^4:
+// 336 us with a lane reading its own links, 116 us with each plane's staged on
+// their own (24 a site), 109 us (with a thread per column, as above, 170: a
+// product of two reads each column's factor again).
 template <int N>
 __global__ __launch_bounds__(192) void k_plaquette_partial(const cplx<double> *__restrict__ U, double *partial,
                                                            Geom g) {
-  using LS = LinkStage<N>;
-  __shared__ cplx<double> buf[3][2][LS::ELEMS];
+  constexpr int S = 32;
+  using LT = LinkTile<N, S, 192>;
+  __shared__ cplx<double> buf[LT::elems(16)];
+  __shared__ unsigned tab[16 * S];
   __shared__ double sh[3];
   const unsigned V = 2 * (unsigned)g.Vh;
   const unsigned blk = xcd_range(blockIdx.x, gridDim.x);
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const unsigned lex = blk * 64 + (threadIdx.x & 63);
-  const Site x(g, lex < V ? lex : V - 1);
-  double s = 0.0;
+  const int p = (int)(threadIdx.x >> 5), s = (int)(threadIdx.x & 31);   // (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+  const int mu = p < 3 ? 0 : p < 5 ? 1 : 2, nu = p < 3 ? p + 1 : p < 5 ? p - 1 : 3;
+  double sum = 0.0;
 #pragma unroll 1
   for (int q = 0; q < 2; ++q) {
-    const int p = 2 * w + q;   // (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-    const int mu = p < 3 ? 0 : p < 5 ? 1 : 2, nu = p < 3 ? p + 1 : p < 5 ? p - 1 : 3;
-    Mat<N> a;
+    const unsigned lex = blk * 64 + q * S + s;
+    const Site x(g, lex < V ? lex : V - 1);
+    if (p < 4) {   // slots a: U_a(x), 4 + 3 b + j: U_a(x+b), a the j-th other than b
+      const unsigned xp = x.lex + x.shift(g, p, 1);
+      tab[p * S + s] = x.lex * 4 + p;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int m = h ? nu : mu, n = h ? mu : nu;
-      LS::fetch(buf[w][0], U, x.lex, m);
-      LS::fetch(buf[w][1], U, x.lex + x.shift(g, m, 1), n);
-      wait_fetch();
-      __syncthreads();
-      const Mat<N> r = mul<N>(LS::read(buf[w][0], false), LS::read(buf[w][1], false));
-      __syncthreads();
-      if (h == 0) {
-        a = r;
-      } else {
-        double tr = 0.0;
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-#pragma unroll
-          for (int j = 0; j < N; ++j) {
-            tr = fma(a.a[i][j].re, r.a[i][j].re, tr);
-            tr = fma(a.a[i][j].im, r.a[i][j].im, tr);
-          }
-        s += tr / N;
-      }
+      for (int j = 0; j < 3; ++j) tab[(4 + 3 * p + j) * S + s] = xp * 4 + j + (j >= p);
     }
+    __syncthreads();
+    LT::template fetch<16>(buf, U, tab);
+    wait_fetch();
+    __syncthreads();
+    const Mat<N> a = mul<N>(ld_mat<N>(LT::at(buf, mu, s), false),
+                            ld_mat<N>(LT::at(buf, 4 + 3 * mu + nu - (nu > mu), s), false));
+    const unsigned i = after<N>(s, a);
+    const Mat<N> b = mul<N>(ld_mat<N>(LT::at(buf, nu, i), false),
+                            ld_mat<N>(LT::at(buf, 4 + 3 * nu + mu - (mu > nu), i), false));
+    double tr = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        tr = fma(a.a[k][j].re, b.a[k][j].re, tr);
+        tr = fma(a.a[k][j].im, b.a[k][j].im, tr);
+      }
+    if (lex < V) sum += tr / N;
+    __syncthreads();
   }
-  s = block_sum(lex < V ? s : 0.0, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  sum = block_sum(sum, sh);
+  if (threadIdx.x == 0) partial[blockIdx.x] = sum;
 }
 
 // Thread per link: U <- exp(i eps pi) U, the exponential by scaling and
@@ -348,8 +265,8 @@ __global__ __launch_bounds__(256) void k_algebra(cplx<double> *pi, const double 
 template <int N>
 static hipError_t gf_launch(const void *U, void *F, const Geom &g, double beta, double scale, int accumulate,
                             hipStream_t st) {
-  const size_t n = 4 * ((2 * (size_t)g.Vh + 63) / 64);   // (64 sites, direction)
-  hipLaunchKernelGGL(k_gauge_force<N>, dim3((unsigned)n), dim3(64), 0, st,
+  const size_t n = g.Vh / 8;   // 16 sites (every extent is even)
+  hipLaunchKernelGGL(k_gauge_force<N>, dim3((unsigned)n), dim3(64 * N), 0, st,
                      (const cplx<double> *)U, (cplx<double> *)F, g, beta, scale, accumulate);
   return hipGetLastError();
 }
