@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, 'csrc')
 BUILD = os.path.join(HERE, '_build')
 LIB = os.path.join(HERE, 'libwdirac.so')
 SOURCES = ['api.hip', 'rep.hip', 'blas.hip', 'force.hip', 'stream.hip', 'clover.hip', 'hmc.hip',
-           'cg_tiny.hip']
+           'cg_tiny.hip', 'hop_clover.hip']
 # (source, WD_PART): each part holds the kernels of some precisions, projectors
 # and representation dimensions (the longest first)
 PARTS = [('hop.hip', k) for k in range(8)] + [('hop_mr.hip', k) for k in range(4)]

@@ -321,11 +321,29 @@ struct CgHop {
   int lcnt2 = 0;
 };
 
+// D_ee in (parity 0) or D_oo^{-1} in (parity 1) with a clover field, lattice
+// by lattice; out may alias in.
+int clover_apply(const wdirac_ctx *c, void *out, const void *in, const void *clov, int parity, int nrhs, int prec,
+                 hipStream_t st) {
+  const size_t cb = prec == WDIRAC_F64 ? 16 : 8;
+  for (int l = 0; l < c->nlat; ++l) {
+    const size_t so = (size_t)4 * c->d * c->spre[l] * cb;
+    const size_t co = (size_t)4 * c->d * (2 * c->d + 1) * c->spre[l] * cb;
+    WD_HIP(wd::launch_clover_apply(static_cast<char *>(out) + so, static_cast<const char *>(in) + so,
+                                   static_cast<const char *>(clov) + co, c->g[l], c->d, parity, nrhs, prec, st));
+  }
+  return WDIRAC_OK;
+}
+
 // One hopping-term launch over every lattice of the context.  counts/prow
 // (nullable) receive the layout of the per-tile partial sums.
+// clov (nullable): out = D_oo^{-1} (beta H in) on the odd sites, out = D_ee cx +
+// beta H in on the even ones (alpha and xadd unused), in the hop's epilogue where
+// one of its forms is launched, else by a pass of its own.
 int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_parity, int dagger, int nrhs,
         double alpha, const void *xadd, double beta, int prec, double *partial, hipStream_t st,
-        wd::Counts *counts = nullptr, int *prow = nullptr, const CgHop *cg = nullptr) {
+        wd::Counts *counts = nullptr, int *prow = nullptr, const CgHop *cg = nullptr, const void *clov = nullptr,
+        const void *cx = nullptr) {
   wdirac_tuned sh = c->tuned[prec][nrhs];
   if (!sh.valid) {
     sh = auto_shape(c, prec, nrhs);
@@ -335,7 +353,15 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
     if (c->tblock != kAuto) sh.tblock = c->tblock;
   }
   if (sh.variant == wd::HOP_MULTI && !hop_mr_reaches(c)) sh.variant = wd::HOP_COLOUR;
+  const bool fused = clov && nrhs == 1 && !c->real && wd::hop_clover_ok(c->d, sh.variant);
+  if (clov && cx && !fused) {
+    WD_TRY(clover_apply(c, out, cx, clov, 0, nrhs, prec, st));
+    xadd = out;
+    alpha = 1.0;
+  }
   wd::HopArgs a;
+  a.clov = clov;
+  a.cx = cx;
   a.out = out;
   a.in = in;
   a.links = UR;
@@ -372,24 +398,14 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
   a.sigma = h.sigma;
   wd::Counts cnt{};
   int pr = 0;
-  WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, sh.variant,
-                        effective_nr(c, sh.nr, nrhs, prec, sh.variant), st, &cnt, &pr));
+  if (fused)
+    WD_HIP(wd::launch_hop_clover(a, c->d, prec, dagger, sh.variant, st, &cnt, &pr));
+  else
+    WD_HIP(wd::launch_hop(a, c->N, c->rep, c->d, c->real, prec, dagger, nrhs, sh.variant,
+                          effective_nr(c, sh.nr, nrhs, prec, sh.variant), st, &cnt, &pr));
+  if (clov && !cx && !fused) WD_TRY(clover_apply(c, out, out, clov, 1, nrhs, prec, st));
   if (counts) *counts = cnt;
   if (prow) *prow = pr;
-  return WDIRAC_OK;
-}
-
-// D_ee in (parity 0) or D_oo^{-1} in (parity 1) with a clover field, lattice
-// by lattice; out may alias in.
-int clover_apply(const wdirac_ctx *c, void *out, const void *in, const void *clov, int parity, int nrhs, int prec,
-                 hipStream_t st) {
-  const size_t cb = prec == WDIRAC_F64 ? 16 : 8;
-  for (int l = 0; l < c->nlat; ++l) {
-    const size_t so = (size_t)4 * c->d * c->spre[l] * cb;
-    const size_t co = (size_t)4 * c->d * (2 * c->d + 1) * c->spre[l] * cb;
-    WD_HIP(wd::launch_clover_apply(static_cast<char *>(out) + so, static_cast<const char *>(in) + so,
-                                   static_cast<const char *>(clov) + co, c->g[l], c->d, parity, nrhs, prec, st));
-  }
   return WDIRAC_OK;
 }
 
@@ -401,12 +417,9 @@ int clover_apply(const wdirac_ctx *c, void *out, const void *in, const void *clo
 int dhat(const wdirac_ctx *c, void *out, const void *in, const void *UR, double m0, int dagger, int nrhs, int prec,
          void *tmp, double *partial, hipStream_t st, wd::Counts *counts = nullptr, int *prow = nullptr,
          const void *clov = nullptr, const CgHop *cg1 = nullptr, const CgHop *cg2 = nullptr) {
-  WD_TRY(hop(c, tmp, in, UR, 1, dagger, nrhs, 0.0, nullptr, 1.0, prec, nullptr, st, nullptr, nullptr, cg1));
-  if (clov) {
-    WD_TRY(clover_apply(c, tmp, tmp, clov, 1, nrhs, prec, st));
-    WD_TRY(clover_apply(c, out, in, clov, 0, nrhs, prec, st));
-    return hop(c, out, tmp, UR, 0, dagger, nrhs, 1.0, out, -1.0, prec, partial, st, counts, prow, cg2);
-  }
+  WD_TRY(hop(c, tmp, in, UR, 1, dagger, nrhs, 0.0, nullptr, 1.0, prec, nullptr, st, nullptr, nullptr, cg1, clov));
+  if (clov)
+    return hop(c, out, tmp, UR, 0, dagger, nrhs, 0.0, nullptr, -1.0, prec, partial, st, counts, prow, cg2, clov, in);
   return hop(c, out, tmp, UR, 0, dagger, nrhs, (4.0 + m0) * (4.0 + m0), in, -1.0, prec, partial, st, counts, prow,
              cg2);
 }
@@ -1639,12 +1652,13 @@ int wdirac_force_eo_clover(const wdirac_ctx *ctx, void *P, const void *x_e, cons
   const hipStream_t st = S(stream);
   const CloverForceWs w = carve_clover_force(ctx, workspace);
   // z_o = D_oo^{-1} D_oe x;  y_e = D_ee x - D_eo z_o = D-hat x;  w_o = D_oo^{-1} D_eo^+ y_e
-  WD_TRY(hop(ctx, w.z_o, x_e, UR64, 1, 0, 1, 0.0, nullptr, 1.0, WDIRAC_F64, nullptr, st));
-  WD_TRY(clover_apply(ctx, w.z_o, w.z_o, clov64, 1, 1, WDIRAC_F64, st));
-  WD_TRY(clover_apply(ctx, w.y_e, x_e, clov64, 0, 1, WDIRAC_F64, st));
-  WD_TRY(hop(ctx, w.y_e, w.z_o, UR64, 0, 0, 1, 1.0, w.y_e, -1.0, WDIRAC_F64, nullptr, st));
-  WD_TRY(hop(ctx, w.w_o, w.y_e, UR64, 1, 1, 1, 0.0, nullptr, 1.0, WDIRAC_F64, nullptr, st));
-  WD_TRY(clover_apply(ctx, w.w_o, w.w_o, clov64, 1, 1, WDIRAC_F64, st));
+  const auto chop = [&](void *out, const void *in, int parity, int dagger, double beta, const void *cx) {
+    return hop(ctx, out, in, UR64, parity, dagger, 1, 0.0, nullptr, beta, WDIRAC_F64, nullptr, st, nullptr, nullptr,
+               nullptr, clov64, cx);
+  };
+  WD_TRY(chop(w.z_o, x_e, 1, 0, 1.0, nullptr));
+  WD_TRY(chop(w.y_e, w.z_o, 0, 0, -1.0, x_e));
+  WD_TRY(chop(w.w_o, w.y_e, 1, 1, 1.0, nullptr));
   const size_t el = ctx->real ? 8 : 16;
   for (int l = 0; l < ctx->nlat; ++l) {
     const size_t so = (size_t)4 * ctx->d * ctx->spre[l] * 16;

@@ -130,6 +130,9 @@ struct HopArgs {
   void *r;
   const void *rin, *ps;
   double sigma;
+  // clover block of the epilogue (hop_clover.hip): packed blocks of both
+  // parities, and the field D_ee multiplies (NULL: the hop's result instead)
+  const void *clov, *cx;
 };
 
 // nr: right-hand sides per block of the colour-split form (1..4; reduced to
@@ -144,6 +147,12 @@ hipError_t launch_hop(const HopArgs &a, int N, int rep, int d, int real, int pre
 // within the LDS budget.
 bool hop_nr_supported(int N, int d, int prec, int variant, int nr);
 bool hop_variant_ok(int N, int rep, int d, int variant);
+// hop_clover.hip: a hop of one right-hand side with the clover block of its
+// output sites, xadd and alpha unused (complex links, d_R = 2, 3, 4, the colour
+// forms of stored links).
+bool hop_clover_ok(int d, int variant);
+hipError_t launch_hop_clover(const HopArgs &a, int d, int prec, int dagger, int variant, hipStream_t st,
+                             Counts *counts, int *prow);
 // hop_mr.hip: the HOP_MULTI form (nr = right-hand sides per block, one of
 // 1, 2, 3, 4, 6, 12, dividing nrhs); built for complex d_R = 3, 6 and real
 // d_R = 3.
