@@ -37,7 +37,7 @@ HBM_PEAK_GBS = 8000.0
 WORKLOAD = 'su3_fund_32x32x32x32'
 TRAFFIC_FILE = os.path.join(ROOT, 'profiles', 'dslash_eo_su3_fund_32x32x32x32_traffic.json')
 HOP_SOURCES = [os.path.join(ROOT, 'paper_2503_06721_amd', 'csrc', f)
-               for f in ('hop.hip', 'hop_mr.hip', 'wd_hop.h', 'wd_common.h')]
+               for f in ('hop.hip', 'hop_mr.hip', 'wd_hop.h', 'wd_hop_cs.h', 'wd_common.h')]
 
 
 def log(msg):
@@ -79,7 +79,7 @@ def device_copy_gbps(torch, n=1 << 28, reps=3):
 
 def hop_sources_sha256():
     """SHA-256 over the sources of the hop kernels and the link layout they
-    read (hop.hip, hop_mr.hip, wd_hop.h, wd_common.h, in that order): a
+    read (hop.hip, hop_mr.hip, wd_hop.h, wd_hop_cs.h, wd_common.h, in that order): a
     traffic record taken on other sources no longer applies."""
     h = hashlib.sha256()
     for p in HOP_SOURCES:

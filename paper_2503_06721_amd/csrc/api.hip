@@ -438,8 +438,8 @@ int pack(const wdirac_ctx *c, void *packed, void *canon, int parity, int nrhs, i
 
 // Workspace of the clover force: the three FP64 half fields of the
 // pseudofermion force (whole batch), then the per-lattice scratch of the
-// largest lattice: F (6 d^2 V), K (12 d^2 V), leaf matrices (24 N^2 V) complex
-// FP64, and the log-det partial sums.
+// largest lattice: F (6 d^2 V), K and the leaf matrices (room for 12 d^2 V and
+// 24 N^2 V) complex FP64, and the log-det partial sums.
 struct CloverForceWs {
   void *z_o, *y_e, *w_o;
   double *F, *K, *G, *Us, *part, *dtmp;

@@ -246,9 +246,9 @@ hipError_t launch_clover_apply(void *out, const void *in, const void *clov, cons
                                int nrhs, int prec, hipStream_t st);
 // Clover contribution to the link force of a functional with variation
 // -2 Re sum_x tr[dM Omega], Omega = X Y^+ (Xe non-null) or cdet D_oo^{-1} on odd
-// sites (Xe NULL); P (+)= coef * force (or its gradient form).  F: 6 d^2 V, K: 12 d^2 V,
-// Gl: 24 N^2 V complex FP64 scratch (F only for the exponential form), Us:
-// 4 N^2 V complex FP64 (structure-of-arrays copy of the links).
+// sites (Xe NULL); P (+)= coef * force (or its gradient form).  Scratch of V
+// sites: F, 6 d^2 complex FP64 (exponential form only); K, 6 d^2 reals; Gl, 24 N^2
+// reals (not FUND); Us, 4 N^2 complex FP64 (structure-of-arrays links).
 hipError_t launch_clover_force(void *P, const void *Xe, const void *Xo, const void *Ye, const void *Yo, const void *U,
                                const void *clov, double *F, double *K, double *Gl, double *Us, const Geom &g, int N, int rep,
                                double m0, double csw, int expo, double cdet, double coef, int gradient, int accumulate,
