@@ -1048,15 +1048,12 @@ __global__ __launch_bounds__(64) void k_clover_insert(const cplx<double> *__rest
   }
 }
 
-// Exponential form: as k_clover_insert with B_c <- L(A_c, B_c) before the K
-// entries, L the Frechet derivative of exp at A = C / (4 + m) along B: scaling
-// by 2^-s (s from the largest column sum of |A|, down to 1/4), Horner for
-// exp(A') and its derivative along B / 2^s (Taylor degree 12, as in the field
-// kernels), then s squarings (e, l) <- (e e, l e + e l).
+// Exponential form, d_R > 3: as k_clover_insert_exp below, with general matrices
+// and (e, l) <- (e e, l e + e l).
 // NB = 2 d_R lanes per (site, chirality block): lane i holds row i of A,
 // Omega and of the iterates and reads the other rows from LDS at each matrix
-// product (one lane holding whole NB x NB matrices spills them to scratch).  64-lane blocks (one wavefront) hold MPB = 64 / NB matrices;
-// the lanes past MPB * NB and past the last matrix follow the barriers and
+// product (one lane holding whole NB x NB matrices spills them to scratch).
+// 64-lane blocks (one wavefront) hold MPB = 64 / NB matrices; the lanes past MPB * NB and past the last matrix follow the barriers and
 // store nothing (the former write no LDS either).  Every barrier is reached
 // the same number of times by all lanes: the squarings run to the block's
 // largest count, a matrix that needs fewer keeping its iterates.
@@ -1233,6 +1230,244 @@ __global__ __launch_bounds__(64) void k_clover_insert_rows(const cplx<double> *X
       k[(size_t)e * V] = 0.5 * acc.re;
       if (b != a2) k[(size_t)(e + 1) * V] = 0.5 * acc.im;
     }
+  }
+}
+
+// Operand of the products below that stays in LDS, 64 lanes side by side.
+template <int NB>
+struct HermLds {
+  cplx<double> *o;   // this lane's upper triangle, 64 entries apart
+  double *d;         // and diagonal
+  static constexpr int kTri = NB * (NB - 1) / 2;
+  __device__ __forceinline__ void put(const Herm<NB> &h, double f) const {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) d[i * 64] = f * h.d[i];
+#pragma unroll
+    for (int k = 0; k < kTri; ++k) o[k * 64] = f * h.o[k];
+  }
+  __device__ __forceinline__ cplx<double> off(int i, int j) const {
+    const cplx<double> v = o[Herm<NB>::at(i < j ? i : j, i < j ? j : i) * 64];
+    return mk(v.re, i < j ? v.im : -v.im);
+  }
+};
+
+// r += a b, of whose entries the diagonal's real part and the upper triangle are
+// formed: sums of products that are Hermitian as a whole.
+template <int NB>
+__device__ __forceinline__ void herm_mac(Herm<NB> &r, const HermLds<NB> &a, const Herm<NB> &b) {
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    cplx<double> row[NB];   // row i of a
+    const double di = a.d[i * 64];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) row[k] = k == i ? mk(di, 0.0) : a.off(i, k);
+    r.d[i] = fma(di, b.d[i], r.d[i]);
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (k != i) {
+        const cplx<double> y = b.off(i, k);   // b_ki = conj(b_ik)
+        r.d[i] = fma(row[k].re, y.re, r.d[i]);
+        r.d[i] = fma(row[k].im, y.im, r.d[i]);
+      }
+#pragma unroll
+    for (int j = i + 1; j < NB; ++j) {
+      cplx<double> &t = r.o[Herm<NB>::at(i, j)];
+      const cplx<double> bij = b.off(i, j);
+      t.re = fma(di, bij.re, t.re);
+      t.im = fma(di, bij.im, t.im);
+      t.re = fma(row[j].re, b.d[j], t.re);
+      t.im = fma(row[j].im, b.d[j], t.im);
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (k != i && k != j) t = cfma(row[k], b.off(k, j), t);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // one row of a at a time
+  }
+}
+
+// Exponential form, d_R <= 3: thread per (site, chirality block), the blocks of a
+// site in adjacent lanes.  As k_clover_insert with B_c <- L(A_c, B_c) before the K
+// entries, L the Frechet derivative of exp at A = C / (4 + m) along B: scaling by
+// 2^-s (s from the largest column sum of |A|, down to 1/4), Horner for
+// e = exp(A') and its derivative l along B / 2^s (Taylor degree 12, as in the
+// field kernels), then s squarings (e, l) <- (e e, l e + e l).  Everything is
+// Hermitian (e_k = 1 + A e_{k+1} / k is a real polynomial in A, and
+// l_k = (B e_{k+1} + A l_{k+1}) / k its derivative along B), so that a product
+// costs its upper triangle; e, l and the sum under way are in registers, A and B
+// in LDS.  Bound by FP64 arithmetic at one wavefront per SIMD.  SU(3) FUND 32^4:
+// 4.99 ms with a lane per row of a general matrix, 1.94 ms.
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) void k_clover_insert_exp(
+    const cplx<double> *Xe, const cplx<double> *Xo, const cplx<double> *Ye, const cplx<double> *Yo,
+    const cplx<double> *__restrict__ clov, const cplx<double> *__restrict__ F, double *__restrict__ K, Geom g,
+    SigmaBlocks S, double m0, double csw, double cdet) {
+  constexpr int NB = 2 * D, TRI = NB * (NB - 1) / 2;
+  __shared__ cplx<double> so[2][TRI * 64];
+  __shared__ double sd[2][NB * 64];
+  const size_t V = 2 * (size_t)g.Vh;
+  const size_t gid = (size_t)blockIdx.x * 64 + threadIdx.x;
+  const bool on = gid < 2 * V;   // lanes past the end repeat the last site and store nothing
+  const int c = (int)(threadIdx.x & 1);
+  const unsigned lex = (unsigned)((on ? gid : 2 * V - 2) >> 1);
+  unsigned r = lex;
+  const int z = (int)(r % g.Z); r /= g.Z;
+  const int y = (int)(r % g.Y); r /= g.Y;
+  const int x = (int)(r % g.X);
+  const int t = (int)(r / g.X);
+  const int par = (t + x + y + z) & 1;
+  const size_t cb = lex >> 1;
+  const HermLds<NB> A{so[0] + threadIdx.x, sd[0] + threadIdx.x}, B{so[1] + threadIdx.x, sd[1] + threadIdx.x};
+  int sq;
+  {
+    // A = (i/4) c_sw sum_p S[p][c] F_p / (4 + m)
+    const double f = 0.25 * csw / (4.0 + m0);
+    Herm<NB> a;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) a.d[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < TRI; ++k) a.o[k] = mk(0.0, 0.0);
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+      cplx<double> fp[D][D];
+#pragma unroll
+      for (int i = 0; i < D; ++i)
+#pragma unroll
+        for (int j = 0; j < D; ++j) fp[i][j] = F[((size_t)p * D * D + i * D + j) * V + lex];
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int tt = s2; tt < 2; ++tt) {
+          const cplx<double> sv = S.v[p][c][s2][tt];
+#pragma unroll
+          for (int i2 = 0; i2 < D; ++i2)
+#pragma unroll
+            for (int j2 = 0; j2 < D; ++j2) {
+              const int i = s2 * D + i2, j = tt * D + j2;
+              if (i == j) {   // Re(i sv fp) = -Im(sv fp)
+                a.d[i] = fma(-sv.re, fp[i2][j2].im, a.d[i]);
+                a.d[i] = fma(-sv.im, fp[i2][j2].re, a.d[i]);
+              } else if (i < j) {
+                cplx<double> &o = a.o[Herm<NB>::at(i, j)];
+                o = cfma(mk(-sv.im, sv.re), fp[i2][j2], o);
+              }
+            }
+        }
+      __builtin_amdgcn_sched_barrier(0);   // one plane's F entries at a time
+    }
+    double nrm = 0.0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      double sum = fabs(a.d[i]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (j != i) {
+          const cplx<double> v = a.off(i, j);
+          sum += sqrt(v.re * v.re + v.im * v.im);
+        }
+      nrm = sum > nrm ? sum : nrm;
+    }
+    sq = exp_squarings(nrm * fabs(f));
+    A.put(a, ldexp(f, -sq));
+  }
+  {
+    Herm<NB> b;
+    const cplx<double> *X = par ? Xo : Xe, *Y = par ? Yo : Ye;
+    const cplx<double> *Mi = clov + (size_t)(2 + c) * (NB * (NB + 1) / 2) * g.stride + cb;
+    cplx<double> xv[NB], yv[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const size_t o = (size_t)(2 * c * D + k) * g.stride + cb;
+      xv[k] = Xe ? X[o] : mk(0.0, 0.0);
+      yv[k] = Xe ? Y[o] : mk(0.0, 0.0);
+    }
+    const double w = par == 1 ? 2.0 * cdet : 0.0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = i; j < NB; ++j) {   // x_i conj(y_j) + y_i conj(x_j), + 2 cdet D_oo^{-1}
+        cplx<double> v = cfma_conj(xv[j], yv[i], cfma_conj(yv[j], xv[i], mk(0.0, 0.0)));
+        if (w != 0.0) v = v + w * Mi[(size_t)tri_index(NB, i, j) * g.stride];
+        if (i == j) b.d[i] = v.re;
+        else b.o[Herm<NB>::at(i, j)] = v;
+      }
+    B.put(b, ldexp(1.0, -sq));
+  }
+  // e_k = 1 + A e_{k+1} / k,  l_k = (B e_{k+1} + A l_{k+1}) / k, from e = 1, l = 0
+  Herm<NB> e, l;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    e.d[i] = 1.0;
+    l.d[i] = 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < TRI; ++k) e.o[k] = l.o[k] = mk(0.0, 0.0);
+#pragma unroll 1
+  for (int k = kTaylor; k >= 1; --k) {
+    const double rk = 1.0 / k;
+    Herm<NB> n;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) n.d[i] = 0.0;
+#pragma unroll
+    for (int q = 0; q < TRI; ++q) n.o[q] = mk(0.0, 0.0);
+    herm_mac<NB>(n, A, l);
+    herm_mac<NB>(n, B, e);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      l.d[i] = rk * n.d[i];
+      n.d[i] = 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < TRI; ++q) {
+      l.o[q] = rk * n.o[q];
+      n.o[q] = mk(0.0, 0.0);
+    }
+    herm_mac<NB>(n, A, e);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) e.d[i] = fma(rk, n.d[i], 1.0);
+#pragma unroll
+    for (int q = 0; q < TRI; ++q) e.o[q] = rk * n.o[q];
+  }
+#pragma unroll 1
+  for (int q = 0; q < sq; ++q) {
+    Herm<NB> n;   // e l + l e: (e l)_ij + conj((e l)_ji)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) n.d[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < TRI; ++k) n.o[k] = mk(0.0, 0.0);
+    A.put(e, 1.0);   // (A and B are done with)
+    B.put(l, 1.0);
+    herm_mac<NB>(n, A, l);
+    herm_mac<NB>(n, B, e);
+    l = n;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) n.d[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < TRI; ++k) n.o[k] = mk(0.0, 0.0);
+    herm_mac<NB>(n, A, e);
+    e = n;
+  }
+  // K entries of the site, the two blocks' halves added across the lane pair
+  // (S.v holds 2 sigma)
+#pragma unroll 1
+  for (int p = 0; p < 6; ++p) {
+    const cplx<double> s00 = S.v[p][c][0][0], s01 = S.v[p][c][0][1], s10 = S.v[p][c][1][0], s11 = S.v[p][c][1][1];
+    double *k = K + (size_t)p * D * D * V + lex;
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+      for (int a2 = b; a2 < D; ++a2) {
+        // sum_st sigma_st (B_c)_(t b),(s a)
+        const auto ent = [&](int i, int j) { return i == j ? mk(l.d[i], 0.0) : l.off(i, j); };
+        cplx<double> v = cfma(s00, ent(b, a2), mk(0.0, 0.0));
+        v = cfma(s01, ent(D + b, a2), v);
+        v = cfma(s10, ent(b, D + a2), v);
+        v = cfma(s11, ent(D + b, D + a2), v);
+        v.re += __shfl_xor(v.re, 1, 64);
+        v.im += __shfl_xor(v.im, 1, 64);
+        const int q = b == a2 ? b : herm_pair(D, b, a2);
+        if (on && c == 0) k[(size_t)q * V] = 0.5 * v.re;
+        if (on && c == 1 && b != a2) k[(size_t)(q + 1) * V] = 0.5 * v.im;
+      }
   }
 }
 
@@ -1738,10 +1973,15 @@ static hipError_t clover_force_nr(void *P, const void *Xe, const void *Xo, const
     const cplx<double> *xe = (const cplx<double> *)Xe, *xo = (const cplx<double> *)Xo, *ye = (const cplx<double> *)Ye,
                        *yo = (const cplx<double> *)Yo, *cl = (const cplx<double> *)clov, *u = (const cplx<double> *)U;
     if (expo) {
-      constexpr int MPB = 64 / (2 * D) / 2 * 2;
-      const dim3 rg((unsigned)((2 * V + MPB - 1) / MPB));
-      hipLaunchKernelGGL((k_clover_insert_rows<D>), rg, dim3(64), 0, st, xe, xo, ye, yo, cl, (const cplx<double> *)F, K,
-                         g, S, m0, csw, cdet);
+      if constexpr (D <= 3) {
+        hipLaunchKernelGGL((k_clover_insert_exp<D>), dim3((unsigned)((2 * V + 63) / 64)), dim3(64), 0, st, xe, xo, ye,
+                           yo, cl, (const cplx<double> *)F, K, g, S, m0, csw, cdet);
+      } else {
+        constexpr int MPB = 64 / (2 * D) / 2 * 2;
+        const dim3 rg((unsigned)((2 * V + MPB - 1) / MPB));
+        hipLaunchKernelGGL((k_clover_insert_rows<D>), rg, dim3(64), 0, st, xe, xo, ye, yo, cl,
+                           (const cplx<double> *)F, K, g, S, m0, csw, cdet);
+      }
     } else if (Xe) {
       hipLaunchKernelGGL((k_clover_insert<D, false>), ig, dim3(64), 0, st, xe, xo, ye, yo, cl, K, g, S, cdet);
     } else {
