@@ -958,8 +958,8 @@ bool clover_supported(int d) { return d == 2 || d == 3 || d == 4 || d == 6; }
 // Hermitian to Hermitian): with the Hermitian sigma_p,
 //   (K_p)_ba = sum_c sum_st (sigma_p)_st (B_c)_(t b),(s a).
 
-// Thread per site (regular clover; the exponential form is
-// k_clover_insert_rows): B = X Y^+ + Y X^+ per chirality block, or (DET)
+// Thread per site (regular clover; the exponential form is k_clover_insert_exp
+// or _rows): B = X Y^+ + Y X^+ per chirality block, or (DET)
 // 2 cdet D_oo^{-1} on the odd sites and 0 on the even ones.  For each entry
 // (b, a), b <= a, the eight entries of B it needs are formed once and summed
 // for the six planes.  Bound by memory: SU(3) FUND 24^4 160 us writing both
