@@ -1,5 +1,5 @@
 // SU(N) matrices in registers and the staging of canonical links
-// [T][X][Y][Z][4][N][N] through LDS (hmc.hip, clover.hip).
+// [T][X][Y][Z][4][N][N] through LDS (hmc.hip).
 #pragma once
 #include "wd_common.h"
 
