@@ -452,9 +452,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // Exchange-method (Gauss-Jordan) inverse with partial pivoting of one NB x NB
 // matrix by NB lanes, lane i holding row i in w; every lane of the 64-lane
 // block calls it (barriers).  Step k takes the row p_k of largest |w_k| not
-// yet taken; afterwards lane p_k, whose `mine` is k, holds w[j] =
-// (A^-1)[k][p_j].  The columns rotate one place per step, so that the step's
-// column is always 0 and w stays in registers.  Returns log|det A|.
+// yet taken (a NaN counts as larger than any number, so that every row is taken
+// once and the NaN reaches all of the inverse); afterwards lane p_k, whose `mine`
+// is k, holds w[j] = (A^-1)[k][p_j].  The columns rotate one place per step, so
+// that the step's column is always 0 and w stays in registers.  Returns
+// log|det A|.
 template <int NB>
 __device__ __forceinline__ double rows_exchange(cplx<double> (&w)[NB], cplx<double> (*sh)[NB + 1], int *perm, int i,
                                                 bool lane_used, int &mine) {
@@ -471,8 +473,9 @@ __device__ __forceinline__ double rows_exchange(cplx<double> (&w)[NB], cplx<doub
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const double v = sh[q][NB].re;
-      p = v > best ? q : p;
-      best = v > best ? v : best;
+      const bool up = v > best || (isnan(v) && !isnan(best));
+      p = up ? q : p;
+      best = up ? v : best;
     }
     ld += 0.5 * log(best);
     if (i == p) {
