@@ -94,11 +94,25 @@ __device__ __forceinline__ void lex_coords(const Geom &g, unsigned lex, int (&c)
 // copy Us[mu][N*N][V] (lexicographic site minor; k_links_soa), so that the
 // lanes of a wavefront, on consecutive sites, read consecutive addresses.  The
 // direction (and plane) is the same for all lanes of a wavefront, so each
-// entry row has a scalar base address and a lane one 32-bit offset (16 bytes a
-// site, below 4 GiB for any lattice whose scratch fits the card).
-template <int N>
-__device__ __forceinline__ void load_link(cplx<double> (&u)[N][N], const cplx<double> *Us, size_t V, unsigned lex,
-                                          int mu, bool dag) {
+// entry row has a scalar base address and a lane one 32-bit byte offset, which
+// reaches kNarrowSites sites of 16 bytes.  Of the calls whose fields and scratch
+// a 288 GB card can hold, only the SU(2) fundamental clover field (1056 bytes a
+// site with FP32 blocks, up to 2.9e8 sites) goes beyond: F_launch gives it 64-bit
+// offsets there.  (The next is SU(2) d_R = 3 at 1712 bytes; a force takes 3136 or
+// more.)
+constexpr size_t kNarrowSites = (size_t)1 << 28;
+template <typename V>
+__device__ __forceinline__ const V *at(const V *base, size_t off) {
+  return base + off;
+}
+template <typename V>
+__device__ __forceinline__ V *at(V *base, size_t off) {
+  return base + off;
+}
+
+template <int N, typename Off>
+__device__ __forceinline__ void load_link(cplx<double> (&u)[N][N], const cplx<double> *Us, size_t V, Off lex, int mu,
+                                          bool dag) {
   const cplx<double> *p = Us + (size_t)__builtin_amdgcn_readfirstlane(mu) * N * N * V;
 #pragma unroll
   for (int i = 0; i < N; ++i)
@@ -176,13 +190,14 @@ __device__ constexpr LeafStep kLeafC[4][4] = {
 };
 
 // F scratch: F[p][A][B] of every site, [6][D][D][V] complex FP64.  Thread per
-// (plane, site), consecutive threads on consecutive sites.
-template <int N, int REP>
+// (plane, site), consecutive threads on consecutive sites.  Off: type of the
+// lanes' site offsets (load_link).
+template <int N, int REP, typename Off>
 __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict__ U, cplx<double> *__restrict__ F,
                                                   Geom g) {
   constexpr int D = rep_dim(N, REP);
   const size_t V = 2 * (size_t)g.Vh;
-  const unsigned gid = blockIdx.x * 256u + threadIdx.x;
+  const unsigned gid = blockIdx.x * 256u + threadIdx.x;   // below 6 V, V < 2^29
   // 64-site chunks, the six planes of a chunk in consecutive wavefronts (the
   // planes that share a link direction read it close together in time)
   const unsigned chunk = gid / 384u;
@@ -215,7 +230,7 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
       for (int f = 0; f < 4; ++f) {
         const LeafStep st = kLeafC[k][f];
         cplx<double> u[N][N];
-        load_link<N>(u, U, V, pn.at(st.a, st.b), st.dir ? nu : mu, st.dag != 0);
+        load_link<N>(u, U, V, (Off)pn.at(st.a, st.b), st.dir ? nu : mu, st.dag != 0);
         if (f == 0) {
 #pragma unroll
           for (int i = 0; i < N; ++i)
@@ -246,7 +261,7 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
       for (int B = 0; B < DA; ++B) {
         const cplx<double> v = FUND ? mk(0.125 * (acc[A][B].re - acc[B][A].re), 0.125 * (acc[A][B].im + acc[B][A].im))
                                     : 0.125 * acc[A][B];
-        *at(Fp + (size_t)(A * D + B) * V, lex) = v;
+        *at(Fp + (size_t)(A * D + B) * V, (Off)lex) = v;
       }
     return;
   }
@@ -257,7 +272,7 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
     for (int f = 0; f < 4; ++f) {
       const LeafStep s = kLeafC[k][f];
       cplx<double> u[N][N];
-      load_link<N>(u, U, V, pn.at(s.a, s.b), s.dir ? nu : mu, s.dag != 0);
+      load_link<N>(u, U, V, (Off)pn.at(s.a, s.b), s.dir ? nu : mu, s.dag != 0);
       if (f == 0) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
@@ -272,7 +287,7 @@ __global__ __launch_bounds__(256) void k_clover_F(const cplx<double> *__restrict
       for (int B = 0; B < D; ++B) {
         const cplx<double> rab = rep_entry<N, REP>(L, A, B), rba = rep_entry<N, REP>(L, B, A);
         cplx<double> v = mk(0.125 * (rab.re - rba.re), 0.125 * (rab.im + rba.im));
-        cplx<double> *o = at(Fp + (size_t)(A * D + B) * V, lex);
+        cplx<double> *o = at(Fp + (size_t)(A * D + B) * V, (Off)lex);
         if (k > 0) v = v + *o;
         *o = v;
       }
@@ -801,8 +816,16 @@ __global__ __launch_bounds__(256) void k_clover_apply(cplx<T> *out, const cplx<T
 template <int N, int REP>
 static hipError_t F_launch(const void *U, double *F, const Geom &g, hipStream_t st) {
   const size_t n = 384 * ((2 * (size_t)g.Vh + 63) / 64);   // six planes per 64-site chunk
-  hipLaunchKernelGGL((k_clover_F<N, REP>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     (const cplx<double> *)U, (cplx<double> *)F, g);
+  const dim3 grid((unsigned)((n + 255) / 256));
+  const cplx<double> *u = (const cplx<double> *)U;
+  cplx<double> *f = (cplx<double> *)F;
+  if constexpr (N == 2 && REP == 0) {
+    if (2 * (size_t)g.Vh > kNarrowSites) {
+      hipLaunchKernelGGL((k_clover_F<N, REP, size_t>), grid, dim3(256), 0, st, u, f, g);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_clover_F<N, REP, unsigned>), grid, dim3(256), 0, st, u, f, g);
   return hipGetLastError();
 }
 
