@@ -136,8 +136,9 @@ struct Carver {
 
 size_t partial_doubles(const wdirac_ctx *c, int nrhs) {
   // rows (one per system, twice for the real and imaginary rows of a dot) of
-  // the longest per-tile row any producer writes: the smallest tiles are the
-  // 32-site tiles of the multi-rhs hop with two lanes per site
+  // the longest row that hops, norms and dots write: the smallest tiles are the
+  // 32-site tiles of the multi-rhs hop with two lanes per site.  (|p|^2 of the
+  // multi-shift recursion has a row of its own: carve_ms.)
   int mx = 0;
   for (int l = 0; l < c->nlat; ++l) mx = std::max(mx, (c->g[l].Vh + 31) / 32);
   return (size_t)2 * nsys_of(c, nrhs) * mx;
@@ -186,7 +187,7 @@ MsWork carve_ms(const wdirac_ctx *c, int nshift, void *ws) {
   w.p = cv.take((size_t)nshift * h);
   w.P1 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
   w.P2 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
-  w.P3 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
+  w.P3 = static_cast<double *>(cv.take(wd::ms_base_blocks(shape(c, 1)) * sizeof(double)));
   w.sc = static_cast<wd::MsScalars *>(cv.take(sizeof(wd::MsScalars)));
   w.bytes = cv.off;
   return w;
@@ -1391,9 +1392,10 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
       }
       // (w.t is only the hop's nominal output: r is stored in its place)
       WD_TRY(dhat(ctx, w.t, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, w.P2, st, &cnt, &prow, nullptr, &ca, &cr));
-      WD_HIP(wd::launch_ms_update_base(xb, pb, cr.r, w.sc, w.P2, cnt.n[0], slot, sigma0 != 0.0 ? w.P3 : nullptr, &npp,
-                                       f, st));
+      WD_HIP(wd::launch_ms_update_base(xb, pb, cr.r, w.sc, w.P2, cnt.n[0], slot, sigma0 != 0.0 ? w.P3 : nullptr, f,
+                                       st));
       pp = w.P3;
+      npp = wd::ms_base_blocks(f);
       if (++slot == wd::MSRING) WD_TRY(flush());
       hop_count += 4;
     }

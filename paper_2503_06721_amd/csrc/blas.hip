@@ -509,12 +509,15 @@ __global__ __launch_bounds__(BT) void k_ms_update_base(cplx<double> *__restrict_
   }
 }
 
+// Components per thread of the base update (as update_xp), and its blocks, each
+// with a partial sum of |p|^2.
+static int ms_base_per(const FieldShape &f) { return blas_nblocks(f) >= 1024 ? f.ncomp : 4; }
+int ms_base_blocks(const FieldShape &f) { return blas_nblocks(f) * (f.ncomp / ms_base_per(f)); }
+
 hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, const double *rr_partial, int cnt,
-                                 int slot, double *pp, int *npp, const FieldShape &f, hipStream_t st) {
-  const int nb = blas_nblocks(f);
-  const int per = nb >= 1024 ? f.ncomp : 4;
-  const dim3 grid(nb, f.ncomp / per);
-  *npp = nb * (f.ncomp / per);
+                                 int slot, double *pp, const FieldShape &f, hipStream_t st) {
+  const int per = ms_base_per(f);
+  const dim3 grid(blas_nblocks(f), f.ncomp / per);
   hipLaunchKernelGGL(k_ms_update_base, grid, dim3(BT), 0, st, (cplx<double> *)x, (cplx<double> *)p,
                      (const cplx<double> *)r, s, rr_partial, cnt, slot, pp, per, f);
   return hipGetLastError();

@@ -224,9 +224,11 @@ hipError_t launch_ms_init(MsScalars *s, const double *b2_partial, int nblk, cons
                           int base, double sigma0, double tol, hipStream_t st);
 // Base shift of an iteration: x += alpha p, p = r + beta p, and the scalars
 // of every shift for ring slot `slot`, beta from the partial sums of |r|^2
-// (cnt of them).  pp (nullable): receives *npp partial sums of the new |p|^2.
+// (cnt of them).  pp (nullable): receives ms_base_blocks() partial sums of the
+// new |p|^2.
+int ms_base_blocks(const FieldShape &f);
 hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, const double *rr_partial, int cnt,
-                                 int slot, double *pp, int *npp, const FieldShape &f, hipStream_t st);
+                                 int slot, double *pp, const FieldShape &f, hipStream_t st);
 // The updates of the other shifts for the n iterations of ring slots 0..n-1
 // (residuals `ring`, MSRING fields fstride apart).
 hipError_t launch_ms_update_xp(void *x, void *p, const void *ring, const MsScalars *s, long long fstride,
