@@ -462,10 +462,25 @@ __device__ __forceinline__ void ms_end_step(MsScalars &s, double rr, int slot) {
   s.cg.active = any;
 }
 
-// Base shift: x += alpha p, p = r + beta p as k_cg_update_xp (OWN), the first
-// block also advancing the scalars of every shift (whose fields no other block
-// reads), and |p|^2 summed on the way where the next step length needs it
-// (sigma0 > 0), which saves a pass over p.
+// The sum and ms_end_step as a kernel of their own.
+__global__ __launch_bounds__(1024) void k_ms_end(MsScalars *S, const double *__restrict__ rr_partial, int cnt,
+                                                 int slot) {
+  MsScalars &s = *S;
+  const int act = s.cg.act_it;
+  const double rr = act ? sum_partials(rr_partial, cnt) : 0.0;
+  ms_end_step(s, rr, slot);
+  if (threadIdx.x == 0) s.cg.rr = rr;
+}
+
+// Base shift: x += alpha p, p = r + beta p as k_cg_update_xp, and |p|^2 summed on
+// the way where the next step length needs it (sigma0 > 0), which saves a pass
+// over p.  Up to kOwnSum partial sums every block adds them up itself (OWN) and
+// the first one also advances the scalars of every shift, whose fields no other
+// block reads; longer rows, whose reads by every block would grow as the square
+// of the volume, are summed by k_ms_end (an iteration of a one-shift solve, every
+// block adding against k_ms_end: SU(3) FUND 32^4, 8192 partial sums, 739 and 734
+// us; SU(2) FUND 64^4, 131072, 9.55 and 8.16 ms).
+template <bool OWN>
 __global__ __launch_bounds__(BT) void k_ms_update_base(cplx<double> *__restrict__ x, cplx<double> *__restrict__ p,
                                                        const cplx<double> *__restrict__ r, MsScalars *S,
                                                        const double *__restrict__ rr_partial, int cnt, int slot,
@@ -474,8 +489,13 @@ __global__ __launch_bounds__(BT) void k_ms_update_base(cplx<double> *__restrict_
   MsScalars &s = *S;
   const int act = s.cg.act_it, xb = s.xb_it;
   const double a = s.cg.alpha, rho = s.cg.rho_it;
-  const double rr = act ? sum_partials(rr_partial, cnt) : 0.0;
-  if (blockIdx.x == 0 && blockIdx.y == 0) ms_end_step(s, rr, slot);
+  double rr = 0.0;
+  if constexpr (OWN) {
+    if (act) rr = sum_partials(rr_partial, cnt);
+    if (blockIdx.x == 0 && blockIdx.y == 0) ms_end_step(s, rr, slot);
+  } else {
+    rr = s.cg.rr;
+  }
   if (!act) return;
   const bool ok = isfinite(rr);
   const double b = rr / rho;
@@ -518,9 +538,14 @@ hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, 
                                  int slot, double *pp, const FieldShape &f, hipStream_t st) {
   const int per = ms_base_per(f);
   const dim3 grid(blas_nblocks(f), f.ncomp / per);
-  hipLaunchKernelGGL(k_ms_update_base, grid, dim3(BT), 0, st, (cplx<double> *)x, (cplx<double> *)p,
-                     (const cplx<double> *)r, s, rr_partial, cnt, slot, pp, per, f);
-  return hipGetLastError();
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(BT), 0, st, (cplx<double> *)x, (cplx<double> *)p, (const cplx<double> *)r, s,
+                       rr_partial, cnt, slot, pp, per, f);
+    return hipGetLastError();
+  };
+  if (cnt <= kOwnSum) return go(k_ms_update_base<true>);
+  hipLaunchKernelGGL(k_ms_end, dim3(1), dim3(1024), 0, st, s, rr_partial, cnt, slot);
+  return go(k_ms_update_base<false>);
 }
 
 // The other shifts, N iterations at once: for every slot j in turn

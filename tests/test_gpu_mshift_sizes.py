@@ -37,3 +37,10 @@ def _check(N, rep, dims, shifts, m0=-0.2, tol=1e-9):
 def test_small_lattices(N, rep, dims):
     """1, 2 and 4 blocks a component group; d_R = 10 and 15."""
     _check(N, rep, dims, [0.02, 0.5])
+
+
+@pytest.mark.parametrize('shifts', [[0.3], [0.05, 0.4, 2.0]])
+def test_long_rows(shifts):
+    """5120 partial sums of |r|^2, more than a block of the base update adds up itself, and 1280 blocks of it with a
+    thread for all components of a site."""
+    _check(2, 'ADJ', (32, 32, 32, 20), shifts)
