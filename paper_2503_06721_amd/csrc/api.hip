@@ -224,25 +224,54 @@ bool hop_mr_reaches(const wdirac_ctx *c) {
 
 // Launch shape of a hop the caller has neither tuned nor set options for, by
 // representation, precision, right-hand sides and size (half-lattice sites
-// Vh).  Times are us per hop, the shape chosen against the colour-split form
-// with one hop per phase and up to four rhs per block, which served every call
-// before.
+// Vh).  Times are us per hop, the shape chosen against the one across the line;
+// where none is named, that is the colour-split form with one hop per phase and
+// up to four rhs per block.
 //  * Two-index links, FP64: the compact form reads N^2 instead of d_R^2
-//    entries per link and rebuilds the others exactly as rep_links computes
-//    them (SU(3) SYM 24^4: 92 against 178, SU(4) 2AS 130 against 179, SU(4)
-//    SYM 188 against 397; 2AS below 16^4 is faster with stored links).  Not in
-//    FP32, where entries rebuilt from rounded links carry a larger error.
+//    entries per link and rebuilds the others by the formula of rep_links from
+//    the same links (SU(3) SYM 24^4: 92 against 178, SU(4) 2AS 130 against 179,
+//    SU(4) SYM 188 against 397; 2AS below 16^4 is faster with stored links).
+//    Not in FP32, where entries rebuilt from rounded links carry a larger error.
+//    d_R = 10 takes two rhs per block as soon as one would leave a CU with two
+//    blocks (SU(4) SYM 8^4, 10 rhs: 26 against 32 with one; 8 rhs, 256 blocks:
+//    18 with one against 26).
 //  * Several rhs at d_R = 6: one wavefront per rhs with the links staged per
 //    block, swept along t over sub-lattices so that neighbours stay in L2
 //    (SU(3) SYM 48x24^3, 12 rhs FP64: 1454 against 2004, FP32 836 against
-//    988).  SYM in FP64 below six rhs, or where no sweep fits, is faster one
-//    rhs per block in the compact form (24^4, 4 rhs: 303 against 350).
+//    988).
+//    - SYM in FP64 is faster one rhs per block in the compact form below six
+//      rhs (24^4, 4 rhs: 303 against 350) and where no sweep fits (18x14^3, 8
+//      rhs: 85 against 88), but for lattices whose compact blocks, three per CU,
+//      take a second round and whose fields still fit the caches (10^4, 12 rhs:
+//      26 against 35; 12^4, 8 rhs: 37 against 44; level at 14^4, 12 rhs: 98).
+//    - FP32 with two or three rhs only on large lattices (24^4, 2 rhs: 113
+//      against 123 for two hops per phase; 20^4: 62 against 52).
+//    - Four, three or two rhs per block, the most that divide nrhs; in FP32 two
+//      on lattices too small for the blocks that larger groups leave, the fewer
+//      the groups the larger (four against two: 4 rhs 32x16^3 74 against 62,
+//      20^4 87 either way, 24^4 163 against 183; 8 rhs 10^4 15.5 against 15.0,
+//      12^4 21.7 against 23.6; 12 rhs 8^4 12.7 against 12.6, 10x14x6x18 22 against
+//      25; three against two: 6 rhs 12^4 17.9 against 17.2, 16x8x12x16 18.0
+//      against 20.2).
+//    - Sub-lattices of three x-rows by three tiles, else four (24^4, 12 rhs FP32:
+//      422 against 434 for four by three); a row of four tiles by two in FP64
+//      (32x16^3, 12 rhs: 299 against 309; 24x16^3 217 against 219; 16^4 186 against
+//      174), by four in FP32 (24x16^3, 8 rhs: 71 against 75).  With fewer than six
+//      rhs only by three tiles (24^4, 4 rhs FP32: 163 against 173 without a sweep;
+//      32x16^3, rows of four tiles: 97 against 62).
 //  * d_R <= 4, one rhs: two or four hops per phase, more loads in flight per
 //    barrier (SU(3) FUND 32^4 FP64: 135 against 155, FP32 79 against 86; 24^4:
-//    51.5 against 53.4; SU(2) FUND 16^4 7.8 against 9.0).  Several rhs in FP64:
-//    two hops per phase with two or three rhs per block (24^4, 12 rhs: SU(3)
-//    FUND 389 against 476, SU(2) ADJ 326 against 440); d_R = 4 on a large
-//    lattice gains only with 2 or 4 rhs (12: 556 against 529).
+//    51.5 against 53.4; SU(2) FUND 16^4 7.8 against 9.0).
+//  * d_R <= 4, several rhs in FP64: two hops per phase with two or three rhs per
+//    block (24^4, 12 rhs: SU(3) FUND 389 against 476, SU(2) ADJ 326 against
+//    440).  d_R = 4 gains with 2 or 4 rhs (24^4, 4 rhs: 196 against 204), two rhs
+//    in blocks of one below 20000 sites (8^4: 7.2 against 8.7; 14^4: 15.3 against
+//    16.4; 24^4: 121 against 114); with others where groups of four fill the
+//    chip poorly (16^4, 12 rhs: 93 against 107; 24^4: 556 against 534; 12^4: 31
+//    against 29; groups of three, 6 rhs: 16^4 51 against 54, 16^3x8 25.5 against
+//    24.0).  SU(2) SYM with 5, 7 or 11 rhs takes stored links on small lattices
+//    (10^4, 5 rhs: 8.0 against 9.1; 10x14x6x18 10.4 against 10.5, 7 rhs 12.7
+//    against 12.4).
 //  * d_R = 15: fewer rhs per block, four spill (SU(4) ADJ 24^4 FP32, 12 rhs:
 //    1788 against 3083).
 //  * XCD ranges are left out where each would start a multiple of 256 KiB
@@ -254,9 +283,13 @@ bool hop_mr_reaches(const wdirac_ctx *c) {
 //    nothing re-reads (SU(4) 2AS 48x24^3 FP32: 179 against 184).
 wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
   const bool f64 = prec == WDIRAC_F64, even = nrhs % 2 == 0;
-  long long Vh = 0;
-  for (int l = 0; l < c->nlat; ++l) Vh += c->g[l].Vh;
+  long long Vh = 0, tiles = 0;   // tiles of 64 sites
+  for (int l = 0; l < c->nlat; ++l) {
+    Vh += c->g[l].Vh;
+    tiles += (c->g[l].Vh + 63) / 64;
+  }
   const bool large = Vh >= 131072;
+  const bool odd = nrhs > 3 && nrhs % 2 && nrhs % 3;   // 5, 7, 11: one rhs per block in every form
   const int d = c->d;
   wdirac_tuned s{1, wd::HOP_COLOUR, 4, 1, 0};
   if (d == 6) {
@@ -265,13 +298,12 @@ wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
     const int nb = g.Y * g.Z % 64 == 0 ? g.Y * g.Z / 64 : 0;
     const int bx = g.X % 3 == 0 ? 3 : g.X % 4 == 0 ? 4 : 2;
     const int by = nb == 0 ? 0 : nb % 3 == 0 ? 3 : nb % 4 == 0 && (nb >= 8 || !f64) ? 4 : nb % 2 == 0 ? 2 : 0;
-    const bool sym = c->rep == WDIRAC_SYM, small = Vh < 75000;
-    const int nr = nrhs % 4 == 0 && (f64 || nrhs == 12 || !small) ? 4
-                   : nrhs % 3 == 0 && (f64 || !even || !small)    ? 3
-                   : even                                         ? 2
-                                                                  : 1;
+    const bool sym = c->rep == WDIRAC_SYM;
+    const bool pairs = !f64 && even && Vh < (nrhs < 6 ? 75000 : nrhs < 8 ? 12288 : nrhs < 12 ? 6000 : 4096);
+    const int nr = pairs ? 2 : nrhs % 4 == 0 ? 4 : nrhs % 3 == 0 ? 3 : even ? 2 : 1;
+    const bool rounds = Vh < 16384 && tiles * nrhs > 768;   // of the compact form's blocks
     const bool multi = nr > 1 && hop_mr_reaches(c) &&
-                       (!f64 ? large || nrhs >= 4 : sym ? nrhs >= 6 && by > 0 : nrhs >= 3);
+                       (!f64 ? large || nrhs >= 4 : sym ? nrhs >= 6 && (by > 0 || rounds) : nrhs >= 3);
     if (multi) {
       s.variant = wd::HOP_MULTI;
       s.nr = nr;
@@ -284,15 +316,16 @@ wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
       s.nr = f64 && even ? 2 : 1;
       if (!f64 && large && c->nlat == 1) s.xcd_remap = 0;
     }
-  } else if (f64 && wd::compact_links_ok(c->N, c->rep)) {   // SYM, d_R = 3 and 10
+  } else if (f64 && wd::compact_links_ok(c->N, c->rep) && !(d == 3 && odd && Vh < 7000)) {   // SYM, d_R = 3 and 10
     s.variant = wd::HOP_COMPACT;
-    s.nr = d == 10 && even ? 2 : 1;
+    s.nr = d == 10 && even && tiles * nrhs > 256 ? 2 : 1;
   } else if (d <= 4 && nrhs == 1) {
     s.variant = f64 ? (d == 2 && !large ? wd::HOP_COLOUR_PAIR : wd::HOP_COLOUR_QUAD)
                     : (d == 3 && !c->real ? wd::HOP_COLOUR_PAIR : wd::HOP_COLOUR_QUAD);
-  } else if (f64 && (d == 2 || d == 3 || (d == 4 && (nrhs == 2 || nrhs == 4 || (!large && (nrhs < 6 || Vh >= 16384)))))) {
+  } else if (f64 && (d == 2 || d == 3 || (d == 4 && (nrhs == 2 || nrhs == 4 || (!large && (nrhs < 6 || Vh >= (nrhs % 4 ? 20000 : 16384))))))) {
+    const bool two = nrhs > 2 || (d == 4 ? Vh >= 20000 : d == 3 && !c->real);   // rhs per block, if even
     s.variant = wd::HOP_COLOUR_PAIR;
-    s.nr = d == 3 && nrhs % 3 == 0 && Vh >= 65536 ? 3 : even && (d == 4 || nrhs > 2 || !(c->real || d == 2)) ? 2 : 1;
+    s.nr = d == 3 && nrhs % 3 == 0 && Vh >= 65536 ? 3 : even && two ? 2 : 1;
   } else if (d == 2 && even && Vh < 262144) {               // FP32
     s.nr = 2;
   } else if (d == 15) {
