@@ -274,13 +274,14 @@ bool hop_mr_reaches(const wdirac_ctx *c) {
 //    against 12.4).
 //  * d_R = 15: fewer rhs per block, four spill (SU(4) ADJ 24^4 FP32, 12 rhs:
 //    1788 against 3083).
-//  * XCD ranges are left out where each would start a multiple of 256 KiB
-//    into every row and the fields outgrow the memory-side cache: the eight
-//    XCDs then stream the same HBM channels at the same time (SU(3) FUND FP64,
-//    32^4: 135 against 147 with ranges, 24x32^3: 103 against 115, 48x32^3: 206
-//    against 233; 24^4, whose ranges do not line up: 51.1 against 51.5; 16^4,
-//    in cache: 12.6 against 11.3), and for the stored links of d_R = 6, which
-//    nothing re-reads (SU(4) 2AS 48x24^3 FP32: 179 against 184).
+//  * XCD ranges are left out where each would start a multiple of 128 KiB into
+//    every row and the fields outgrow the memory-side cache: the eight XCDs then
+//    stream the same HBM channels at the same time (SU(3) FUND 32^4 FP64 135
+//    against 147 with ranges, FP32 79 against 87; 24x32^3: 103 against 115, FP32
+//    62 against 64; 36x32^3, a multiple in FP64 alone: 168 against 175, FP32 99
+//    against 93; 24^4, whose ranges do not line up: 51.6 either way; 16^4, in
+//    cache: 12.6 against 11.5), and for the stored links of d_R = 6, which
+//    nothing re-reads (SU(4) 2AS 48x24^3 FP32: 178 against 185).
 wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
   const bool f64 = prec == WDIRAC_F64, even = nrhs % 2 == 0;
   long long Vh = 0, tiles = 0;   // tiles of 64 sites
@@ -335,7 +336,7 @@ wdirac_tuned auto_shape(const wdirac_ctx *c, int prec, int nrhs) {
     s.nr = 1;
   }
   // (one rhs only: the rhs groups of a tile share its links in one XCD's L2)
-  if (c->nlat == 1 && nrhs == 1 && Vh >= 262144 && Vh % 131072 == 0 && (f64 || d < 15)) s.xcd_remap = 0;
+  if (c->nlat == 1 && nrhs == 1 && Vh >= 262144 && Vh % (f64 ? 65536 : 131072) == 0 && (f64 || d < 15)) s.xcd_remap = 0;
   return s;
 }
 

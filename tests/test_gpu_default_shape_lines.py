@@ -22,3 +22,9 @@ pytestmark = pytest.mark.gpu
     (4, 'FUND', (16, 16, 16, 8), 0, 6), (4, 'FUND', (20, 14, 14, 14), 0, 6)])
 def test_lines(N, rep, dims, prec, nrhs):
     _compare(N, rep, dims, prec, nrhs)
+
+
+@pytest.mark.parametrize('prec', [0, 1])
+def test_xcd_ranges(prec):
+    """327680 half-lattice sites: XCD ranges 640 KiB (FP64) and 320 KiB long."""
+    _compare(2, 'FUND', (20, 32, 32, 32), prec, 1)
