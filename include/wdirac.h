@@ -142,7 +142,11 @@ int wdirac_destroy(wdirac_ctx *ctx);
  *   WDIRAC_OPT_XCD_REMAP               1 = give each XCD a contiguous range of
  *                                      site tiles
  *   WDIRAC_OPT_CG_CHECK_EVERY          CG iterations between host checks of
- *                                      convergence (default 4, 1..1000)
+ *                                      convergence (1..1000; where it is not
+ *                                      set 4, and 512 for FP64 solves on
+ *                                      lattices of up to 512 (even site,
+ *                                      colour) pairs, d_R = 2 to 4, whose
+ *                                      iterations run inside one kernel)
  *   WDIRAC_OPT_MIXED_DELTA             reliable-update trigger of mixed CG,
  *                                      ||r|| < delta max ||r|| (default 0.01)
  *   WDIRAC_OPT_TILE_TBLOCK             0 = site tiles in lexicographic

@@ -32,7 +32,7 @@ struct wdirac_ctx {
   wdirac_tuned tuned[2][13];   // autotuned shape per (precision, nrhs)
   int xcd_remap;
   int tblock;           // t-blocked tile order (0 = lexicographic)
-  int cg_check_every;   // CG iterations between host convergence checks
+  int cg_check_every;   // CG iterations between host convergence checks (kAuto: check_every)
   double mixed_delta;   // reliable-update trigger ||r|| < delta max||r||
   int cg_graph;         // replay the CG iterations between checks as a HIP graph
   int tune_compact;     // the autotuner also times the compact-link forms
@@ -74,6 +74,13 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 size_t half_bytes(const wdirac_ctx *c, int nrhs, int prec) {
   return (size_t)nrhs * 4 * c->d * c->spre[c->nlat] * (prec == WDIRAC_F64 ? 16 : 8);
+}
+
+// CG iterations between host checks: the caller's, or 4; 512 where one kernel
+// runs them all and stops by itself (SU(2) FUND 4^4: an iteration 7.9 us, a check
+// between kernels 21).
+int check_every(const wdirac_ctx *c, bool one_kernel) {
+  return c->cg_check_every != kAuto ? c->cg_check_every : one_kernel ? 512 : 4;
 }
 
 // Independent systems of a packed field: the right-hand sides of a single
@@ -567,8 +574,7 @@ int wdirac_create_batch(wdirac_ctx **ctx, int Ng, int rep, const wdirac_geom *ge
   }
   c->hop_variant[0] = c->hop_variant[1] = c->hop_nr[0] = c->hop_nr[1] = kAuto;
   std::memset(c->tuned, 0, sizeof(c->tuned));
-  c->xcd_remap = c->tblock = kAuto;
-  c->cg_check_every = 4;
+  c->xcd_remap = c->tblock = c->cg_check_every = kAuto;
   c->mixed_delta = 0.01;
   c->cg_graph = 1;
   c->tune_compact = 1;
@@ -1139,13 +1145,12 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
   }
   WD_HIP(wd::launch_lincomb(p, 1.0, r, 0.0, nullptr, f, prec, st));
   const double delta = mixed ? ctx->mixed_delta : 0.0;
-  const int check = ctx->cg_check_every;
   int rc = WDIRAC_OK;
   int launched = 0;   // iterations launched since start
   // lattices that fit one workgroup iterate inside one kernel until they stop
   // (mixed mode: from check to check, where replacements are decided)
   const bool tiny = ctx->nlat == 1 && !clov64 && wd::cg_tiny_ok(ctx->g[0], ctx->d, ctx->real);
-  constexpr int kTinyIters = 512;
+  const int check = check_every(ctx, tiny && !mixed);
   int seen_iters = 0;   // hops counted so far (tiny)
   bool use_graph = ctx->cg_graph && st == ctx->own && !tiny;
   hipGraphExec_t exec = nullptr;
@@ -1183,7 +1188,7 @@ static int cg_impl(const wdirac_ctx *ctx, void *x, const void *b, const void *UR
       rc = WDIRAC_ENOCONV;
       break;
     }
-    const int nit = std::min(tiny && !mixed ? kTinyIters : check, std::max(1, maxit - max_iters));
+    const int nit = std::min(check, std::max(1, maxit - max_iters));
     if (tiny) {
       const double m4 = (4.0 + m0) * (4.0 + m0);
       WD_HIP(wd::launch_cg_tiny(xi, p, r, UR, ctx->g[0], ctx->d, ctx->real, w.sc, m4, delta, nit, nrhs, prec, st));
@@ -1404,7 +1409,7 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
       rc = WDIRAC_ENOCONV;
       break;
     }
-    const int nit = std::min(ctx->cg_check_every, std::max(1, maxit - hs.cg.iters));
+    const int nit = std::min(check_every(ctx, false), std::max(1, maxit - hs.cg.iters));
     for (int it = 0; it < nit; ++it) {
       wd::Counts cnt{};
       int prow = 0;
