@@ -176,8 +176,15 @@ CgWork carve_cg(const wdirac_ctx *c, int nrhs, int mode, void *ws) {
   return w;
 }
 
+// Residuals that a multi-shift solve keeps.  Each costs a half field of workspace
+// and defers the updates of the nshift - 1 other shifts, so few shifts keep few
+// (SU(3) FUND 32^4, us an iteration with 3, this many and 8 residuals: 2 shifts
+// 810, 810, 793; 4 shifts 886, 858, 839; 12 shifts 1220, 1036, 1036).  Two shifts
+// then need 7 half fields, no more than with an update in every iteration.
+int ms_ring(int nshift) { return nshift == 1 ? 1 : std::min(wd::MSRING, nshift + 1); }
+
 struct MsWork {
-  void *r, *t, *u, *v, *p;   // FP64 half fields; r holds a ring of residuals, p nshift fields
+  void *r, *t, *u, *p;       // FP64 half fields; r holds a ring of residuals, p nshift fields
   int ring;                  // residuals kept: one where only the base shift needs them
   double *P1, *P2, *P3;
   wd::MsScalars *sc;
@@ -188,9 +195,9 @@ MsWork carve_ms(const wdirac_ctx *c, int nshift, void *ws) {
   Carver cv{static_cast<char *>(ws)};
   MsWork w{};
   const size_t h = half_bytes(c, 1, WDIRAC_F64);
-  w.ring = nshift > 1 ? wd::MSRING : 1;
+  w.ring = ms_ring(nshift);
   w.r = cv.take((size_t)w.ring * h);
-  w.t = cv.take(h); w.u = cv.take(h); w.v = cv.take(h);
+  w.t = cv.take(h); w.u = cv.take(h);
   w.p = cv.take((size_t)nshift * h);
   w.P1 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
   w.P2 = static_cast<double *>(cv.take(partial_doubles(c, 1) * sizeof(double)));
@@ -1429,13 +1436,13 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
         cr.ps = pb;
         cr.sigma = sigma0;
       }
-      // (w.t is only the hop's nominal output: r is stored in its place)
-      WD_TRY(dhat(ctx, w.t, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, w.P2, st, &cnt, &prow, nullptr, &ca, &cr));
+      // (w.u is only the hop's nominal output: r is stored in its place)
+      WD_TRY(dhat(ctx, w.u, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.t, w.P2, st, &cnt, &prow, nullptr, &ca, &cr));
       WD_HIP(wd::launch_ms_update_base(xb, pb, cr.r, w.sc, w.P2, cnt.n[0], slot, sigma0 != 0.0 ? w.P3 : nullptr, f,
                                        st));
       pp = w.P3;
       npp = wd::ms_base_blocks(f);
-      if (++slot == wd::MSRING) WD_TRY(flush());
+      if (++slot == w.ring) WD_TRY(flush());
       hop_count += 4;
     }
   }
@@ -1451,7 +1458,7 @@ int wdirac_cg_mshift_eo(const wdirac_ctx *ctx, void *x, const void *b, const voi
     cr.ps = field(x, k);
     cr.sigma = shifts[k];
     WD_TRY(dhat(ctx, w.u, field(x, k), UR64, m0, 0, 1, WDIRAC_F64, w.t, nullptr, st));
-    WD_TRY(dhat(ctx, w.t, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.v, w.P2, st, &cnt, &prow, nullptr, nullptr, &cr));
+    WD_TRY(dhat(ctx, w.u, w.u, UR64, m0, 1, 1, WDIRAC_F64, w.t, w.P2, st, &cnt, &prow, nullptr, nullptr, &cr));
     WD_HIP(wd::launch_finalize_sum(w.P1, w.P2, prow, cnt, 1, 1, st));
     WD_HIP(hipMemcpyAsync(&res2[k], w.P1, sizeof(double), hipMemcpyDeviceToHost, st));
     hop_count += 4;

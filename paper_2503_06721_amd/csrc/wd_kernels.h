@@ -74,7 +74,7 @@ struct CgScalars {
 // Multi-shift CG (see blas.hip for the recurrences).  One system (one rhs of
 // a single lattice); shift k's fields are `fstride` complex elements apart.
 constexpr int MAXSHIFT = 32;
-// Iterations whose updates of x_k and p_k (k not the base shift) are applied
+// Most iterations whose updates of x_k and p_k (k not the base shift) are applied
 // together, from as many residuals kept in a ring.
 constexpr int MSRING = 8;
 struct ShiftList {
@@ -230,7 +230,7 @@ int ms_base_blocks(const FieldShape &f);
 hipError_t launch_ms_update_base(void *x, void *p, const void *r, MsScalars *s, const double *rr_partial, int cnt,
                                  int slot, double *pp, const FieldShape &f, hipStream_t st);
 // The updates of the other shifts for the n iterations of ring slots 0..n-1
-// (residuals `ring`, MSRING fields fstride apart).
+// (residuals `ring`, n fields fstride apart).
 hipError_t launch_ms_update_xp(void *x, void *p, const void *ring, const MsScalars *s, long long fstride,
                                const FieldShape &f, int n, hipStream_t st);
 
