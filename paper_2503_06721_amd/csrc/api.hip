@@ -401,7 +401,8 @@ int hop(const wdirac_ctx *c, void *out, const void *in, const void *UR, int out_
     if (c->xcd_remap != kAuto) sh.xcd_remap = c->xcd_remap;
     if (c->tblock != kAuto) sh.tblock = c->tblock;
   }
-  if (sh.variant == wd::HOP_MULTI && !hop_mr_reaches(c)) sh.variant = wd::HOP_COLOUR;
+  // (the multi-rhs form loads whole 16-byte link entries directly into LDS)
+  if (sh.variant == wd::HOP_MULTI && (!hop_mr_reaches(c) || ((size_t)UR & 15))) sh.variant = wd::HOP_COLOUR;
   const bool fused = clov && nrhs == 1 && !c->real && wd::hop_clover_ok(c->d, sh.variant);
   if (clov && cx && !fused) {
     WD_TRY(clover_apply(c, out, cx, clov, 0, nrhs, prec, st));

@@ -22,10 +22,10 @@ namespace wd {
 // three links staged, 6.6 GB through L2 at 16 TB/s, half of every line unused;
 // 355 us from this tile with a thread per link, 2.8 GB but four wavefronts a
 // CU; 289 us.
-template <int N>
+template <int N, bool DIRECT>
 __global__ __launch_bounds__(64 * N) void k_gauge_force(const cplx<double> *__restrict__ U, cplx<double> *F, Geom g,
                                                         double beta, double scale, int accumulate) {
-  using LT = LinkTile<N, 16, 64 * N>;
+  using LT = LinkTile<N, 16, 64 * N, DIRECT>;
   constexpr int E = N * N;
   __shared__ cplx<double> buf[LT::elems(16)];
   __shared__ unsigned tab[(16 + 12 + 16) * 16];
@@ -108,11 +108,11 @@ __global__ __launch_bounds__(64 * N) void k_gauge_force(const cplx<double> *__re
 // 336 us with a lane reading its own links, 116 us with each plane's staged on
 // their own (24 a site), 109 us (with a thread per column, as above, 170: a
 // product of two reads each column's factor again).
-template <int N>
+template <int N, bool DIRECT>
 __global__ __launch_bounds__(192) void k_plaquette_partial(const cplx<double> *__restrict__ U, double *partial,
                                                            Geom g) {
   constexpr int S = 32;
-  using LT = LinkTile<N, S, 192>;
+  using LT = LinkTile<N, S, 192, DIRECT>;
   __shared__ cplx<double> buf[LT::elems(16)];
   __shared__ unsigned tab[16 * S];
   __shared__ double sh[3];
@@ -266,9 +266,12 @@ template <int N>
 static hipError_t gf_launch(const void *U, void *F, const Geom &g, double beta, double scale, int accumulate,
                             hipStream_t st) {
   const size_t n = g.Vh / 8;   // 16 sites (every extent is even)
-  hipLaunchKernelGGL(k_gauge_force<N>, dim3((unsigned)n), dim3(64 * N), 0, st,
-                     (const cplx<double> *)U, (cplx<double> *)F, g, beta, scale, accumulate);
-  return hipGetLastError();
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(64 * N), 0, st, (const cplx<double> *)U, (cplx<double> *)F, g,
+                       beta, scale, accumulate);
+    return hipGetLastError();
+  };
+  return direct_ok(U) ? go(k_gauge_force<N, true>) : go(k_gauge_force<N, false>);
 }
 
 hipError_t launch_gauge_force(const void *U, void *F, const Geom &g, int N, double beta, double scale,
@@ -284,15 +287,20 @@ hipError_t launch_gauge_force(const void *U, void *F, const Geom &g, int N, doub
 // (at most kinetic_blocks, which sizes the workspace)
 int plaquette_blocks(const Geom &g) { return (int)((2 * (size_t)g.Vh + 63) / 64); }
 
+template <int N>
+static hipError_t plaq_launch(const void *U, double *partial, const Geom &g, hipStream_t st) {
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(plaquette_blocks(g)), dim3(192), 0, st, (const cplx<double> *)U, partial, g);
+    return hipGetLastError();
+  };
+  return direct_ok(U) ? go(k_plaquette_partial<N, true>) : go(k_plaquette_partial<N, false>);
+}
+
 hipError_t launch_plaquette_partial(const void *U, double *partial, const Geom &g, int N, hipStream_t st) {
-  const dim3 grid(plaquette_blocks(g));
   switch (N) {
-    case 2: hipLaunchKernelGGL(k_plaquette_partial<2>, grid, dim3(192), 0, st, (const cplx<double> *)U, partial, g);
-      return hipGetLastError();
-    case 3: hipLaunchKernelGGL(k_plaquette_partial<3>, grid, dim3(192), 0, st, (const cplx<double> *)U, partial, g);
-      return hipGetLastError();
-    case 4: hipLaunchKernelGGL(k_plaquette_partial<4>, grid, dim3(192), 0, st, (const cplx<double> *)U, partial, g);
-      return hipGetLastError();
+    case 2: return plaq_launch<2>(U, partial, g, st);
+    case 3: return plaq_launch<3>(U, partial, g, st);
+    case 4: return plaq_launch<4>(U, partial, g, st);
   }
   return hipErrorInvalidValue;
 }

@@ -89,8 +89,10 @@ struct Vec {
 // fetch consecutive entries, directly into LDS.  Slot k holds the link
 // tab[k S + s] (4 site + direction) of every tile site s in a row of N^2 16-byte
 // entries, padded to an odd number: lanes on consecutive sites read without
-// bank conflicts.
-template <int N, int S, int NT>
+// bank conflicts.  DIRECT loads take whole 16-byte entries; links whose address is
+// not a multiple of 16 go through registers.
+inline bool direct_ok(const void *U) { return ((size_t)U & 15) == 0; }
+template <int N, int S, int NT, bool DIRECT>
 struct LinkTile {
   static constexpr int E = N * N, ROW = E | 1;
   static constexpr int elems(int slots) { return slots * S * ROW; }
@@ -102,8 +104,13 @@ struct LinkTile {
 #pragma unroll 4
     for (int k = w; k < n; k += NT / 64) {
       const int f = k * 64 + lane, r = f / ROW, q = f - r * ROW, e = q < E ? q : E - 1;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(U + (size_t)tab[r] * E + e),
-                                       (__attribute__((address_space(3))) void *)(buf + k * 64), 16, 0, 0);
+      if constexpr (DIRECT) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(U + (size_t)tab[r] * E + e),
+                                         (__attribute__((address_space(3))) void *)(buf + k * 64), 16, 0, 0);
+      } else {
+        const double *p = reinterpret_cast<const double *>(U) + 2 * ((size_t)tab[r] * E + e);
+        buf[f] = mk(p[0], p[1]);
+      }
     }
   }
   static __device__ __forceinline__ const cplx<double> *at(const cplx<double> *buf, int slot, int s) {
