@@ -77,7 +77,7 @@ size_t half_bytes(const wdirac_ctx *c, int nrhs, int prec) {
 }
 
 // CG iterations between host checks: the caller's, or 4; 512 where one kernel
-// runs them all and stops by itself (SU(2) FUND 4^4: an iteration 7.9 us, a check
+// runs them all and stops by itself (SU(2) FUND 4^4: an iteration 7.5 us, a check
 // between kernels 21).
 int check_every(const wdirac_ctx *c, bool one_kernel) {
   return c->cg_check_every != kAuto ? c->cg_check_every : one_kernel ? 512 : 4;

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(1024) void k_cg_end(CgScalars *S, const double *__r
 //
 // Bound by memory: x, p read and written, r read (5 half fields; with r's own
 // update in the hop an iteration moves 6 beside its hops instead of 9 and a
-// stored A p): 6.1 TB/s on SU(3) FUND 32^4 (FP32 41 us, where the separate
+// stored A p): 6.4 TB/s on SU(3) FUND 32^4 (FP32 40 us, where the separate
 // x, r and p updates took 72).  Up to kOwnSum partial sums every block adds
 // them up itself (OWN), which costs less than a launch between the hop and
 // this kernel; the first block of a system then stores the state, whose

@@ -6,13 +6,14 @@
 // hold a block or two each, and the gaps between them: bound by launches and
 // latency.  A thread holds one colour of one site, its components of r in
 // registers; x, p, u = D-hat p and the odd fields are in LDS (64 KB FP32,
-// 128 KB FP64), links come from L2 ahead of the barrier of their hop.  A solve
-// to 1e-10, per iteration (launched: 36 us SU(2), 48 to 100 us with 12 rhs):
-// SU(2) FUND 4^4 12.6 us, SU(3) FUND 17.4, SU(2) ADJ 16.3, SU(4) FUND 22.4, and
-// 5 to 13% more with 12 rhs, now bound by the LDS reads (8 d spinor components
-// per thread and hop).  Larger lattices fill the LDS or the registers of one CU
+// 128 KB FP64), links come from L2 ahead of the barrier of their hop.  One more
+// iteration of a solve (launched: 36 us SU(2), 48 to 100 us with 12 rhs): SU(2)
+// FUND 4^4 7.5 us, SU(3) FUND 12.2, SU(2) ADJ 11.4, SU(4) FUND 17.0, and up to
+// 3% more with 12 rhs, now bound by the LDS reads (8 d spinor components per
+// thread and hop); the solve itself, with its residuals in FP64, takes 140 to
+// 156 us (162 to 233 with 12 rhs) whatever the iterations.  Larger lattices fill the LDS or the registers of one CU
 // and go back to one launch per hop.  (Twice the threads, each half of them with
-// half of the directions: 11.8 us SU(2) 4^4, but 22 to 34 us for the others.)
+// half of the directions: SU(2) 4^4 6% faster, the others 5 to 50% slower.)
 #include "wd_common.h"
 #include "wd_hop.h"
 #include "wd_kernels.h"

@@ -21,7 +21,7 @@ namespace wd {
 // own links; 404 us with a direction of 64 sites per wavefront and each staple's
 // three links staged, 6.6 GB through L2 at 16 TB/s, half of every line unused;
 // 355 us from this tile with a thread per link, 2.8 GB but four wavefronts a
-// CU; 289 us.
+// CU; 282 us.
 template <int N, bool DIRECT>
 __global__ __launch_bounds__(64 * N) void k_gauge_force(const cplx<double> *__restrict__ U, cplx<double> *F, Geom g,
                                                         double beta, double scale, int accumulate) {
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * N) void k_gauge_force(const cplx<double> *__re
 // site).  tr P = sum_ij a_ij conj(b_ij), a = U_mu(x) U_nu(x+mu), b = U_nu(x)
 // U_mu(x+nu), the 16 links of a site staged once for its planes.  SU(3) 24^4:
 // 336 us with a lane reading its own links, 116 us with each plane's staged on
-// their own (24 a site), 109 us (with a thread per column, as above, 170: a
+// their own (24 a site), 107 us (with a thread per column, as above, 170: a
 // product of two reads each column's factor again).
 template <int N, bool DIRECT>
 __global__ __launch_bounds__(192) void k_plaquette_partial(const cplx<double> *__restrict__ U, double *partial,

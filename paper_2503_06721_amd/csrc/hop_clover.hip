@@ -5,8 +5,8 @@
 //
 // As passes of its own a clover block costs 33 us on SU(3) FUND 24^4 (672 bytes
 // of matrix and 384 of spinor a site, at the copy rate) beside 52 us for a hop;
-// in the epilogue the spinor's two passes are gone (78 us a hop with its
-// block).  A wavefront holds one colour row of 64 sites: the rows of the
+// in the epilogue the spinor's two passes are gone (68 us a hop with its
+// block, launched back to back).  A wavefront holds one colour row of 64 sites: the rows of the
 // vector that M multiplies meet in the hop's LDS, and each lane forms its four
 // spins, reading the rows of M it needs from the packed triangle (an entry off
 // the diagonal serves two wavefronts of the block, the second through L1 or L2).
